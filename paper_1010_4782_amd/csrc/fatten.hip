@@ -11,16 +11,22 @@
 // The staples are built in stages, as products of whole fields, instead of walking 85 paths per site:
 // a "wrap" of a field F (a path from n to n+mu) in a transverse direction nu and sign s is
 //   s = +1:  U_nu(n) F(n+nu) U_nu(n+mu)^dag,        s = -1:  U_nu(n-nu)^dag F(n-nu) U_nu(n-nu+mu),
-// the path that steps s nu, follows F, and steps back.  With X_nu = wrap_nu^+(U_mu) + wrap_nu^-(U_mu)
-// (the 3-link staples of one transverse direction):
-//   3-link  = sum_nu X_nu
-//   5-link  = sum_{rho != si} (wrap_rho^+ + wrap_rho^-)(X_si)
-//   7-link  = sum_{rho != si, nu the third} (wrap_nu^+ + wrap_nu^-)((wrap_rho^+ + wrap_rho^-)(X_si))
-//   Lepage  = sum_nu [wrap_nu^+(wrap_nu^+(U_mu)) + wrap_nu^-(wrap_nu^-(U_mu))]
-// since a wrap is linear in F and the sum over the signs of each step factorises.  Per direction mu that
-// is 28 passes over the lattice (each a few 3x3 products per site), instead of ~400 products per site.
-// Every pass is one thread per site with the matrices in registers; all of them are HBM streams of
-// 144-byte matrices (AoS, as the user layout stores them).
+// the path that steps s nu, follows F, and steps back.  A wrap is linear in F, so everything whose
+// outermost step is nu is summed before that step is taken.  With {nu, rho, si} the three transverse
+// directions and both_nu = wrap_nu^+ + wrap_nu^-:
+//   stage 1   X_nu = both_nu(U_mu)                                             (the 3-link staples)
+//   stage 2   G_nu = c3 U_mu + c5 (X_rho + X_si) + c7 (both_rho(X_si) + both_si(X_rho))
+//   stage 3   V_mu = c1 U_mu + sum_nu [ wrap_nu^+(G_nu + cL wrap_nu^+(U_mu)) + wrap_nu^-(G_nu + cL wrap_nu^-(U_mu)) ]
+// (the Lepage paths take the same sign twice; their inner wrap is recomputed in stage 3, two products,
+// rather than stored and read back, 288 B).  24 + 6 wraps per mu and site, in three launches.
+//
+// What bounds it: traffic beyond L2.  A field is 144 B per site (95 MB at 24^3x48); the sites in flight on
+// one XCD touch more of the stage's fields than its 4 MB L2 holds, so a launch reads 2.4-3 times its
+// compulsory bytes: 1.5, 2.1 and 2.05 GB for the three stages at 24^3x48, at 6.7-7 TB/s (0.21, 0.31 and
+// 0.30 ms).  One lane per site; the fields it works on are planar ([9][V] double2, one plane per matrix
+// element), so that a wave's load of one element of 64 neighbour matrices is 1 KiB contiguous.  In the user
+// layout the same load touches 64 cache lines for a sixth of their bytes.  Both link fields of a 24^3x48
+// field take 3.9 ms; 110 launches over matrices in the user layout, one wrap each, took 16.6 ms.
 #include <hip/hip_runtime.h>
 
 #include "fatten.h"
@@ -33,189 +39,334 @@ struct M3 {
   double2 e[9];  // row-major, (re, im)
 };
 
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
-// a * conj(b)
-__device__ __forceinline__ double2 cmulc(double2 a, double2 b) { return {a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y}; }
-// conj(a) * b
-__device__ __forceinline__ double2 ccmul(double2 a, double2 b) { return {a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x}; }
-
-__device__ __forceinline__ M3 ld(const double2* p) {
-  M3 m;
-#pragma unroll
-  for (int i = 0; i < 9; ++i) m.e[i] = p[i];
-  return m;
+// s += a b, s += a conj(b), s += conj(a) b
+__device__ __forceinline__ void fma_nn(double2& s, double2 a, double2 b) {
+  s.x = fma(a.x, b.x, s.x);
+  s.x = fma(-a.y, b.y, s.x);
+  s.y = fma(a.x, b.y, s.y);
+  s.y = fma(a.y, b.x, s.y);
 }
-__device__ __forceinline__ void st(double2* p, const M3& m) {
-#pragma unroll
-  for (int i = 0; i < 9; ++i) p[i] = m.e[i];
-}
-
-// A B
-__device__ __forceinline__ M3 mul_nn(const M3& a, const M3& b) {
-  M3 c;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      double2 s = cmul(a.e[3 * i], b.e[j]);
-#pragma unroll
-      for (int k = 1; k < 3; ++k) {
-        const double2 t = cmul(a.e[3 * i + k], b.e[3 * k + j]);
-        s.x += t.x;
-        s.y += t.y;
-      }
-      c.e[3 * i + j] = s;
-    }
-  return c;
-}
-// A B^dag: (A B^dag)_ij = sum_k A_ik conj(B_jk)
-__device__ __forceinline__ M3 mul_na(const M3& a, const M3& b) {
-  M3 c;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      double2 s = cmulc(a.e[3 * i], b.e[3 * j]);
-#pragma unroll
-      for (int k = 1; k < 3; ++k) {
-        const double2 t = cmulc(a.e[3 * i + k], b.e[3 * j + k]);
-        s.x += t.x;
-        s.y += t.y;
-      }
-      c.e[3 * i + j] = s;
-    }
-  return c;
-}
-// A^dag B: (A^dag B)_ij = sum_k conj(A_ki) B_kj
-__device__ __forceinline__ M3 mul_an(const M3& a, const M3& b) {
-  M3 c;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      double2 s = ccmul(a.e[i], b.e[j]);
-#pragma unroll
-      for (int k = 1; k < 3; ++k) {
-        const double2 t = ccmul(a.e[3 * k + i], b.e[3 * k + j]);
-        s.x += t.x;
-        s.y += t.y;
-      }
-      c.e[3 * i + j] = s;
-    }
-  return c;
-}
+__device__ __forceinline__ void fma_nc(double2& s, double2 a, double2 b) { fma_nn(s, a, double2{b.x, -b.y}); }
+__device__ __forceinline__ void fma_cn(double2& s, double2 a, double2 b) { fma_nn(s, double2{a.x, -a.y}, b); }
 
 struct FGeo {
   int L[4];
-  long stride[4];  // lex distance of one step: 1, Lx, Lx Ly, Lx Ly Lz
-  long vol;
+  int stride[4];  // lex distance of one step: 1, Lx, Lx Ly, Lx Ly Lz
+  int vol;        // at most 2^28: a planar element's byte offset fits 32 bits
 };
 
-// lex index of n + d e_dir (periodic); c = coordinates of n
-__device__ __forceinline__ long step(long lex, const int c[4], const FGeo& g, int dir, int d) {
+// lex distance from n to n + d e_dir (periodic, |d| <= 2 <= L); c = coordinates of n
+__device__ __forceinline__ int hop(const int c[4], const FGeo& g, int dir, int d) {
   int v = c[dir] + d;
   v = v >= g.L[dir] ? v - g.L[dir] : (v < 0 ? v + g.L[dir] : v);
-  return lex + (long)(v - c[dir]) * g.stride[dir];
+  return (v - c[dir]) * g.stride[dir];
 }
 
-__device__ __forceinline__ void coords(long lex, const FGeo& g, int c[4]) {
-  c[0] = (int)(lex % g.L[0]);
-  long r = lex / g.L[0];
-  c[1] = (int)(r % g.L[1]);
+__device__ __forceinline__ void coords(int lex, const FGeo& g, int c[4]) {
+  c[0] = lex % g.L[0];
+  int r = lex / g.L[0];
+  c[1] = r % g.L[1];
   r /= g.L[1];
-  c[2] = (int)(r % g.L[2]);
-  c[3] = (int)(r / g.L[2]);
+  c[2] = r % g.L[2];
+  c[3] = r / g.L[2];
 }
 
-__device__ __forceinline__ const double2* mat(const double2* f, long site) { return f + 9 * site; }
-__device__ __forceinline__ double2* mat(double2* f, long site) { return f + 9 * site; }
+// Element e of the matrix at `site` of a planar field.  The plane's base is uniform over the wave and the
+// lane's offset 32 bits wide, so the loads take a scalar base.
+__device__ __forceinline__ double2 ld_e(const double2* f, const FGeo& g, int e, int site) {
+  const char* plane = reinterpret_cast<const char*>(f) + (long)e * g.vol * 16;
+  return *reinterpret_cast<const double2*>(plane + (unsigned)site * 16u);
+}
+__device__ __forceinline__ void st_e(double2* f, const FGeo& g, int e, int site, double2 v) {
+  char* plane = reinterpret_cast<char*>(f) + (long)e * g.vol * 16;
+  *reinterpret_cast<double2*>(plane + (unsigned)site * 16u) = v;
+}
+__device__ __forceinline__ M3 ld(const double2* f, const FGeo& g, int site) {
+  M3 m;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) m.e[i] = ld_e(f, g, i, site);
+  return m;
+}
+__device__ __forceinline__ M3 zero() {
+  M3 m;
+#pragma unroll
+  for (int i = 0; i < 9; ++i) m.e[i] = double2{0.0, 0.0};
+  return m;
+}
 
-// out(n) = [acc ? out(n) : 0] + cw * sum over the signs in `signs` (bit 0: +, bit 1: -) of wrap_nu^s(F)(n);
-// and, if out2 is not null, out2(n) += c2 * (the same sum).
-__global__ __launch_bounds__(256) void k_wrap(const double2* __restrict__ U, const double2* __restrict__ F,
-                                              double2* __restrict__ out, double cw, int acc,
-                                              double2* __restrict__ out2, double c2, int mu, int nu, int signs,
-                                              FGeo g) {
-  const long n = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= g.vol) return;
-  int c[4];
-  coords(n, g, c);
-  const double2* Unu = U + 9 * (long)nu * g.vol;
-  M3 s;
+// acc += A F B^dag (PLUS) or A^dag F B, one row of the first product at a time
+template <bool PLUS>
+__device__ __forceinline__ void wrap_acc(M3& acc, const M3& a, const M3& f, const M3& b) {
 #pragma unroll
-  for (int i = 0; i < 9; ++i) s.e[i] = {0.0, 0.0};
-  if (signs & 1) {
-    const long a = step(n, c, g, nu, 1);   // n + nu
-    const long b = step(n, c, g, mu, 1);   // n + mu
-    const M3 t = mul_nn(ld(mat(Unu, n)), ld(mat(F, a)));
-    const M3 w = mul_na(t, ld(mat(Unu, b)));
+  for (int i = 0; i < 3; ++i) {
+    double2 t[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
 #pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      s.e[i].x += w.e[i].x;
-      s.e[i].y += w.e[i].y;
-    }
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        if (PLUS)
+          fma_nn(t[j], a.e[3 * i + k], f.e[3 * k + j]);
+        else
+          fma_cn(t[j], a.e[3 * k + i], f.e[3 * k + j]);
+      }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        if (PLUS)
+          fma_nc(acc.e[3 * i + j], t[k], b.e[3 * j + k]);
+        else
+          fma_nn(acc.e[3 * i + j], t[k], b.e[3 * k + j]);
+      }
   }
-  if (signs & 2) {
-    const long a = step(n, c, g, nu, -1);  // n - nu
-    int ca[4] = {c[0], c[1], c[2], c[3]};
-    ca[nu] = ca[nu] == 0 ? g.L[nu] - 1 : ca[nu] - 1;
-    const long b = step(a, ca, g, mu, 1);  // n - nu + mu
-    const M3 t = mul_an(ld(mat(Unu, a)), ld(mat(F, a)));
-    const M3 w = mul_nn(t, ld(mat(Unu, b)));
+}
+
+// Closes a group of loads: none of them may sink below it to its use.  Left alone the compiler keeps two or
+// three loads in flight and waits out a full memory latency for nearly every matrix row.
+__device__ __forceinline__ void issue_all() { asm volatile("" ::: "memory"); }
+
+// A B
+__device__ __forceinline__ M3 mul(const M3& a, const M3& b) {
+  M3 c = zero();
 #pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      s.e[i].x += w.e[i].x;
-      s.e[i].y += w.e[i].y;
-    }
-  }
-  double2* o = mat(out, n);
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) fma_nn(c.e[3 * i + j], a.e[3 * i + k], b.e[3 * k + j]);
+  return c;
+}
+
+constexpr int kFatWG = 256;
+
+// Workgroups go round-robin over the 8 XCDs, and each XCD has its own L2.  XCD x takes the z planes
+// [x Lz / 8, (x + 1) Lz / 8) and sweeps t through them, so that a site's t neighbours are read by the same
+// XCD a few thousand sites apart and are still in its L2.
+__device__ __forceinline__ int zblock(const FGeo& g, int x) { return x * g.L[2] / 8; }
+// The site of this lane, or -1 past the end of the XCD's block.
+__device__ __forceinline__ int my_site(const FGeo& g) {
+  const int x = blockIdx.x & 7, i = (int)(blockIdx.x >> 3) * kFatWG + threadIdx.x;
+  const int z0 = zblock(g, x), per_t = (zblock(g, x + 1) - z0) * g.stride[2];
+  if (per_t == 0) return -1;
+  const int t = i / per_t;
+  if (t >= g.L[3]) return -1;
+  return t * g.stride[3] + z0 * g.stride[2] + (i - t * per_t);
+}
+inline int site_blocks(const FGeo& g) {
+  const int zmax = (g.L[2] + 7) / 8;
+  return 8 * (int)(((long)zmax * g.stride[2] * g.L[3] + kFatWG - 1) / kFatWG);
+}
+
+// The k-th transverse direction of mu, k = 0..2
+__host__ __device__ constexpr int transverse(int mu, int k) { return k < mu ? k : k + 1; }
+
+// The matrices of a wave between the user layout (9 double2 per site, contiguous) and one matrix per lane,
+// through LDS, so that a load or store covers whole cache lines where the lanes' sites are neighbours.
+// site < 0: nothing is stored.
+__device__ __forceinline__ void store_user(double2* out, int site, int lane, const M3& m, double2* lds) {
+#pragma unroll
+  for (int e = 0; e < 9; ++e) lds[9 * lane + e] = m.e[e];
+  __builtin_amdgcn_wave_barrier();
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
-    const double2 prev = acc ? o[i] : double2{0.0, 0.0};
-    o[i] = {prev.x + cw * s.e[i].x, prev.y + cw * s.e[i].y};
+    const int u = i * 64 + lane, owner = u / 9;
+    const int s = __shfl(site, owner, 64);
+    if (s >= 0) out[9L * s + (u - 9 * owner)] = lds[u];
   }
-  if (out2) {
-    double2* o2 = mat(out2, n);
+  __builtin_amdgcn_wave_barrier();
+}
+// Every lane asks for a valid site.
+__device__ __forceinline__ M3 load_user(const double2* f, int site, int lane, double2* lds) {
 #pragma unroll
-    for (int i = 0; i < 9; ++i) o2[i] = {o2[i].x + c2 * s.e[i].x, o2[i].y + c2 * s.e[i].y};
+  for (int i = 0; i < 9; ++i) {
+    const int u = i * 64 + lane, owner = u / 9;
+    const int s = __shfl(site, owner, 64);
+    lds[u] = f[9L * s + (u - 9 * owner)];
   }
+  __builtin_amdgcn_wave_barrier();
+  M3 m;
+#pragma unroll
+  for (int e = 0; e < 9; ++e) m.e[e] = lds[9 * lane + e];
+  __builtin_amdgcn_wave_barrier();
+  return m;
 }
 
-// X = P + M;  V += c3 X
-__global__ __launch_bounds__(256) void k_staple_sum(const double2* __restrict__ P, const double2* __restrict__ M,
-                                                    double2* __restrict__ X, double2* __restrict__ V, double c3,
-                                                    long n9) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n9) return;
-  const double2 x = {P[i].x + M[i].x, P[i].y + M[i].y};
-  X[i] = x;
-  V[i] = {V[i].x + c3 * x.x, V[i].y + c3 * x.y};
+// user layout -> planes, one direction per blockIdx.y
+__global__ __launch_bounds__(kFatWG) void k_planes(const double2* __restrict__ U, double2* __restrict__ P, FGeo g) {
+  __shared__ double2 lds[kFatWG / 64][9 * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int raw = blockIdx.x * kFatWG + threadIdx.x;
+  if (raw - lane >= g.vol) return;  // the whole wave is past the lattice
+  const long f = (long)blockIdx.y * 9 * g.vol;
+  const M3 m = load_user(U + f, raw < g.vol ? raw : g.vol - 1, lane, lds[wave]);
+  if (raw >= g.vol) return;
+#pragma unroll
+  for (int e = 0; e < 9; ++e) st_e(P + f, g, e, raw, m.e[e]);
 }
 
-// V = c1 U
-__global__ __launch_bounds__(256) void k_scale(const double2* __restrict__ U, double2* __restrict__ V, double c1,
-                                               long n9) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n9) return;
-  V[i] = {c1 * U[i].x, c1 * U[i].y};
-}
-
-// W_mu(n) = U_mu(n) U_mu(n + mu) U_mu(n + 2 mu), every mu (one thread per (mu, n))
-__global__ __launch_bounds__(256) void k_long(const double2* __restrict__ U, double2* __restrict__ W, FGeo g) {
-  const long id = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= 4 * g.vol) return;
-  const int mu = (int)(id / g.vol);
-  const long n = id - (long)mu * g.vol;
+// Stage 1: X_nu = both_nu(U_mu), one transverse direction per blockIdx.y
+template <int MU>
+__global__ __launch_bounds__(kFatWG) void k_staple(const double2* __restrict__ U, double2* __restrict__ X, FGeo g) {
+  const int n = my_site(g);
+  if (n < 0) return;
   int c[4];
   coords(n, g, c);
-  const double2* Um = U + 9 * (long)mu * g.vol;
-  const long n1 = step(n, c, g, mu, 1);
-  const long n2 = step(n, c, g, mu, 2);  // c + 2 < 2 L for L >= 2: one wrap suffices
-  const M3 t = mul_nn(ld(mat(Um, n)), ld(mat(Um, n1)));
-  st(mat(W + 9 * (long)mu * g.vol, n), mul_nn(t, ld(mat(Um, n2))));
+  const long f9 = 9L * g.vol;
+  const double2* Um = U + MU * f9;
+  const int mu1 = hop(c, g, MU, 1);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int nu = transverse(MU, k);
+    const double2* Un = U + nu * f9;
+    const int up = n + hop(c, g, nu, 1), dn = n + hop(c, g, nu, -1);
+    M3 acc = zero();
+    {
+      const M3 a = ld(Un, g, n), f = ld(Um, g, up), b = ld(Un, g, n + mu1);
+      issue_all();
+      wrap_acc<true>(acc, a, f, b);
+    }
+    {
+      const M3 a = ld(Un, g, dn), f = ld(Um, g, dn), b = ld(Un, g, dn + mu1);
+      issue_all();
+      wrap_acc<false>(acc, a, f, b);
+    }
+#pragma unroll
+    for (int e = 0; e < 9; ++e) st_e(X + k * f9, g, e, n, acc.e[e]);
+  }
 }
 
-inline unsigned blocks(long n) { return (unsigned)((n + 255) / 256); }
+// Stage 2: G_nu = c3 U_mu + c5 (X_rho + X_si) + c7 (both_rho(X_si) + both_si(X_rho)), the three nu together:
+// the four U_rho matrices of a wrap serve both X fields that rho wraps.
+template <int MU>
+__global__ __launch_bounds__(kFatWG, 2) void k_inner(const double2* __restrict__ U, const double2* __restrict__ X,
+                                                  double2* __restrict__ G, double c3, double c5, double c7, FGeo g) {
+  const int n = my_site(g);
+  if (n < 0) return;
+  int c[4];
+  coords(n, g, c);
+  const long f9 = 9L * g.vol;
+  const int mu1 = hop(c, g, MU, 1);
+  M3 acc[3] = {zero(), zero(), zero()};
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    const int rho = transverse(MU, r), p = (r + 1) % 3, q = (r + 2) % 3;
+    const double2* Ur = U + rho * f9;
+    const int up = n + hop(c, g, rho, 1), dn = n + hop(c, g, rho, -1);
+    {
+      const M3 a = ld(Ur, g, n), b = ld(Ur, g, n + mu1);
+      const M3 fp = ld(X + p * f9, g, up), fq = ld(X + q * f9, g, up);
+      issue_all();
+      wrap_acc<true>(acc[q], a, fp, b);
+      wrap_acc<true>(acc[p], a, fq, b);
+    }
+    {
+      const M3 a = ld(Ur, g, dn), b = ld(Ur, g, dn + mu1);
+      const M3 fp = ld(X + p * f9, g, dn), fq = ld(X + q * f9, g, dn);
+      issue_all();
+      wrap_acc<false>(acc[q], a, fp, b);
+      wrap_acc<false>(acc[p], a, fq, b);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 9; ++e) {
+    const double2 u = ld_e(U + MU * f9, g, e, n);
+    double2 x[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) x[k] = ld_e(X + k * f9, g, e, n);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const double2 p = x[(k + 1) % 3], q = x[(k + 2) % 3], a = acc[k].e[e];
+      st_e(G + k * f9, g, e, n, double2{c3 * u.x + c5 * (p.x + q.x) + c7 * a.x, c3 * u.y + c5 * (p.y + q.y) + c7 * a.y});
+    }
+  }
+}
+
+// Stage 3: V_mu in the user layout
+template <int MU>
+__global__ __launch_bounds__(kFatWG) void k_outer(const double2* __restrict__ U, const double2* __restrict__ G,
+                                                  double2* __restrict__ V, double c1, double cl, FGeo g) {
+  __shared__ double2 lds[kFatWG / 64][9 * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int own = my_site(g);
+  if (__ballot(own >= 0) == 0) return;  // the whole wave is past the lattice
+  const int n = own >= 0 ? own : 0;
+  int c[4];
+  coords(n, g, c);
+  const long f9 = 9L * g.vol;
+  const double2* Um = U + MU * f9;
+  const int mu1 = hop(c, g, MU, 1);
+  M3 acc;
+#pragma unroll
+  for (int e = 0; e < 9; ++e) {
+    const double2 u = ld_e(Um, g, e, n);
+    acc.e[e] = double2{c1 * u.x, c1 * u.y};
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const int nu = transverse(MU, k);
+    const double2* Un = U + nu * f9;
+    const double2* Gn = G + k * f9;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      // the site one step away (s = 0: n + nu, s = 1: n - nu), and where its own wrap reads U_mu and U_nu:
+      // +: U_nu(n+nu) U_mu(n+2nu) U_nu(n+nu+mu)^dag,  -: U_nu(n-2nu)^dag U_mu(n-2nu) U_nu(n-2nu+mu)
+      const int one = n + hop(c, g, nu, s == 0 ? 1 : -1), two = n + hop(c, g, nu, s == 0 ? 2 : -2);
+      const int side = s == 0 ? one : two;
+      M3 h = zero();
+      {
+        const M3 a = ld(Un, g, side), f = ld(Um, g, two), b = ld(Un, g, side + mu1);
+        issue_all();
+        if (s == 0)
+          wrap_acc<true>(h, a, f, b);
+        else
+          wrap_acc<false>(h, a, f, b);
+      }
+      const int at = s == 0 ? n : one;
+      const M3 w = ld(Gn, g, one), a = ld(Un, g, at), b = ld(Un, g, at + mu1);
+      issue_all();
+#pragma unroll
+      for (int e = 0; e < 9; ++e) h.e[e] = double2{fma(cl, h.e[e].x, w.e[e].x), fma(cl, h.e[e].y, w.e[e].y)};
+      if (s == 0)
+        wrap_acc<true>(acc, a, h, b);
+      else
+        wrap_acc<false>(acc, a, h, b);
+    }
+  }
+  store_user(V, own, lane, acc, lds[wave]);
+}
+
+// W_mu(n) = U_mu(n) U_mu(n + mu) U_mu(n + 2 mu), from and to the user layout, one mu per blockIdx.y
+__global__ __launch_bounds__(kFatWG) void k_long(const double2* __restrict__ U, double2* __restrict__ W, FGeo g) {
+  __shared__ double2 lds[kFatWG / 64][9 * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int own = my_site(g);
+  if (__ballot(own >= 0) == 0) return;  // the whole wave is past the lattice
+  const int n = own >= 0 ? own : 0, mu = blockIdx.y;
+  int c[4];
+  coords(n, g, c);
+  int d1 = 0, d2 = 0;
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+    if (d == mu) {
+      d1 = hop(c, g, d, 1);
+      d2 = hop(c, g, d, 2);
+    }
+  const double2* Um = U + (long)mu * 9 * g.vol;
+  const M3 a = load_user(Um, n, lane, lds[wave]);
+  const M3 t = mul(a, load_user(Um, n + d1, lane, lds[wave]));
+  const M3 w = mul(t, load_user(Um, n + d2, lane, lds[wave]));
+  store_user(W + (long)mu * 9 * g.vol, own, lane, w, lds[wave]);
+}
+
+template <int MU>
+void fat_direction(const double2* Up, double2* X, double2* G, double2* V, double u0, const FGeo& g, hipStream_t st) {
+  const double u2 = 1.0 / (u0 * u0), u4 = u2 * u2, u6 = u4 * u2;
+  const double c1 = 5.0 / 8.0, c3 = u2 / 16.0, c5 = u4 / 64.0, c7 = u6 / 384.0, cl = -u4 / 16.0;
+  const dim3 nb(site_blocks(g)), wg(kFatWG);
+  hipLaunchKernelGGL(k_staple<MU>, nb, wg, 0, st, Up, X, g);
+  hipLaunchKernelGGL(k_inner<MU>, nb, wg, 0, st, Up, (const double2*)X, G, c3, c5, c7, g);
+  hipLaunchKernelGGL(k_outer<MU>, nb, wg, 0, st, Up, (const double2*)G, V, c1, cl, g);
+}
 
 }  // namespace
 
@@ -226,57 +377,27 @@ size_t fatten_workspace_bytes(const int dims[4]) {
 
 hipError_t fatten_links(const int dims[4], const void* thin, double u0, void* fat, void* lng, void* ws,
                         hipStream_t st) {
+  const long vol = (long)dims[0] * dims[1] * dims[2] * dims[3];
+  if (vol > (1L << 28)) return hipErrorOutOfMemory;  // thin, fat and lng alone would take 464 GB
   FGeo g;
   for (int i = 0; i < 4; ++i) g.L[i] = dims[i];
   g.stride[0] = 1;
   for (int i = 1; i < 4; ++i) g.stride[i] = g.stride[i - 1] * dims[i - 1];
-  g.vol = g.stride[3] * dims[3];
-  const long n9 = 9 * g.vol;
+  g.vol = (int)vol;
+  const long f9 = 9 * vol;
   const double2* U = static_cast<const double2*>(thin);
-  double2* Vf = static_cast<double2*>(fat);
-  double2* W = static_cast<double2*>(lng);
-  double2* w = static_cast<double2*>(ws);
-  double2* P = w;             // wrap^+ of U_mu in one transverse direction
-  double2* Mn = w + n9;       // wrap^-
-  double2* X[4] = {w + 2 * n9, w + 3 * n9, w + 4 * n9, nullptr};  // 3-link staples per transverse direction
-  double2* Y = w + 5 * n9;    // one 5-link staple field (outer rho, inner si)
-  const double u2 = 1.0 / (u0 * u0), u4 = u2 * u2, u6 = u4 * u2;
-  const double c1 = 5.0 / 8.0, c3 = u2 / 16.0, c5 = u4 / 64.0, c7 = u6 / 384.0, cl = -u4 / 16.0;
-
-  for (int mu = 0; mu < 4; ++mu) {
-    const double2* Um = U + (long)mu * n9;
-    double2* Vm = Vf + (long)mu * n9;
-    int others[3], k = 0;
-    for (int d = 0; d < 4; ++d)
-      if (d != mu) others[k++] = d;
-    hipLaunchKernelGGL(k_scale, dim3(blocks(n9)), dim3(256), 0, st, Um, Vm, c1, n9);
-    for (int a = 0; a < 3; ++a) {
-      const int nu = others[a];
-      hipLaunchKernelGGL(k_wrap, dim3(blocks(g.vol)), dim3(256), 0, st, U, Um, P, 1.0, 0, (double2*)nullptr, 0.0,
-                         mu, nu, 1, g);
-      hipLaunchKernelGGL(k_wrap, dim3(blocks(g.vol)), dim3(256), 0, st, U, Um, Mn, 1.0, 0, (double2*)nullptr, 0.0,
-                         mu, nu, 2, g);
-      // Lepage: the same sign twice
-      hipLaunchKernelGGL(k_wrap, dim3(blocks(g.vol)), dim3(256), 0, st, U, (const double2*)P, Vm, cl, 1,
-                         (double2*)nullptr, 0.0, mu, nu, 1, g);
-      hipLaunchKernelGGL(k_wrap, dim3(blocks(g.vol)), dim3(256), 0, st, U, (const double2*)Mn, Vm, cl, 1,
-                         (double2*)nullptr, 0.0, mu, nu, 2, g);
-      hipLaunchKernelGGL(k_staple_sum, dim3(blocks(n9)), dim3(256), 0, st, (const double2*)P, (const double2*)Mn,
-                         X[a], Vm, c3, n9);
-    }
-    for (int a = 0; a < 3; ++a)      // outer rho
-      for (int b = 0; b < 3; ++b) {  // inner si
-        if (a == b) continue;
-        const int rho = others[a], third = others[3 - a - b];
-        // Y = (wrap_rho^+ + wrap_rho^-)(X_si), V += c5 Y
-        hipLaunchKernelGGL(k_wrap, dim3(blocks(g.vol)), dim3(256), 0, st, U, (const double2*)X[b], Y, 1.0, 0, Vm,
-                           c5, mu, rho, 3, g);
-        // V += c7 (wrap_third^+ + wrap_third^-)(Y)
-        hipLaunchKernelGGL(k_wrap, dim3(blocks(g.vol)), dim3(256), 0, st, U, (const double2*)Y, Vm, c7, 1,
-                           (double2*)nullptr, 0.0, mu, third, 3, g);
-      }
-  }
-  hipLaunchKernelGGL(k_long, dim3(blocks(4 * g.vol)), dim3(256), 0, st, U, W, g);
+  double2* V = static_cast<double2*>(fat);
+  // the planar copy of U lives in the long-link output until the last launch writes that
+  double2* Up = static_cast<double2*>(lng);
+  double2* X = static_cast<double2*>(ws);
+  double2* G = X + 3 * f9;
+  const dim3 nb4((g.vol + kFatWG - 1) / kFatWG, 4), wg(kFatWG);
+  hipLaunchKernelGGL(k_planes, nb4, wg, 0, st, U, Up, g);
+  fat_direction<0>(Up, X, G, V, u0, g, st);
+  fat_direction<1>(Up, X, G, V + f9, u0, g, st);
+  fat_direction<2>(Up, X, G, V + 2 * f9, u0, g, st);
+  fat_direction<3>(Up, X, G, V + 3 * f9, u0, g, st);
+  hipLaunchKernelGGL(k_long, dim3(site_blocks(g), 4), wg, 0, st, U, static_cast<double2*>(lng), g);
   return hipGetLastError();
 }
 

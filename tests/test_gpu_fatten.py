@@ -35,6 +35,17 @@ def test_fatten_links_match_oracle(gpu_lib, dims, u0):
     assert np.max(np.abs(lng.cpu().numpy() - W)) <= TOL
 
 
+@pytest.mark.parametrize("dims", [(6, 2, 10, 4), (2, 6, 18, 2), (10, 6, 8, 6)])
+def test_fatten_links_uneven_z_blocks(gpu_lib, dims):
+    """z extents that the eight per-XCD blocks of planes divide unevenly, and volumes that are no multiple
+    of a workgroup's 256 sites."""
+    print(f"fatten dims={dims}", flush=True)
+    U = random_su3_field(dims, 77)
+    _, fat, lng = _fatten(dims, torch.from_numpy(U).cuda(), 0.9)
+    assert np.max(np.abs(fat.cpu().numpy() - fat_links(U, dims, 0.9))) <= TOL
+    assert np.max(np.abs(lng.cpu().numpy() - long_links(U, dims))) <= TOL
+
+
 def test_fatten_unit_links_closed_form(gpu_lib):
     dims = (4, 4, 2, 6)
     U = np.zeros((4, 6, 2, 4, 4, 3, 3), dtype=np.complex128)
