@@ -132,6 +132,7 @@ hipError_t net_forward(stag_net_s* n, const void* in, void* out, hipStream_t st)
   n->nz[0] = {true, false};
   for (int l = 0; l < n->layers; ++l) {
     const bool last = l == n->layers - 1;
+    NetLaunch L{};
     for (int p = 0; p < (last ? 1 : 2); ++p) {
       NetLayerArgs a = layer_args(n, p);
       a.in_same = n->nz[l][p] ? act_par(n, l, p) : nullptr;
@@ -139,10 +140,11 @@ hipError_t net_forward(stag_net_s* n, const void* in, void* out, hipStream_t st)
       if (!a.in_same && !a.in_other) continue;
       a.out = act_par(n, l + 1, p);
       a.w = wptr(n, n->woff[l]);
-      e = launch_net_layer(a, n->ch[l], n->ch[l + 1], st);
-      if (e != hipSuccess) return e;
+      L.a[L.n++] = a;
       n->nz[l + 1][p] = true;
     }
+    e = launch_net_layer(L, n->ch[l], n->ch[l + 1], st);
+    if (e != hipSuccess) return e;
   }
   if (!out) return hipSuccess;
   if (!n->nz[n->layers][0]) return hipMemsetAsync(out, 0, (size_t)half * 48, st);
@@ -181,18 +183,21 @@ hipError_t net_backward_pair(stag_net_s* n, const void* b, const void* x, double
   }
   for (int l = n->layers - 1; l >= 0; --l) {
     const int ci = n->ch[l], co = n->ch[l + 1];
+    NetLaunch W{};
     for (int p = 0; p < 2; ++p) {
       NetLayerArgs a = layer_args(n, p);
       a.in_same = n->nz[l][p] ? act_par(n, l, p) : nullptr;
       a.in_other = n->nz[l][1 - p] ? act_par(n, l, 1 - p) : nullptr;
-      const float2* gy = gnz[p] ? grad_par(n, cur, co, p) : nullptr;
-      e = launch_net_wgrad(a, gy, part, ci, co, kWgradBlocks, st);
-      if (e != hipSuccess) return e;
+      W.gy[W.n] = gnz[p] ? grad_par(n, cur, co, p) : nullptr;
+      W.a[W.n++] = a;
     }
+    e = launch_net_wgrad(W, part, ci, co, kWgradBlocks, st);
+    if (e != hipSuccess) return e;
     e = launch_net_wgrad_reduce(part, ci, co, kWgradBlocks, 2, reinterpret_cast<double*>(n->gacc.ptr) + gofs[l], st);
     if (e != hipSuccess) return e;
     if (l == 0) break;
     std::array<bool, 2> nnz = {false, false};
+    NetLaunch L{};
     for (int p = 0; p < 2; ++p) {
       NetLayerArgs a = layer_args(n, p);
       a.in_same = gnz[p] ? grad_par(n, cur, co, p) : nullptr;
@@ -200,10 +205,11 @@ hipError_t net_backward_pair(stag_net_s* n, const void* b, const void* x, double
       if (!a.in_same && !a.in_other) continue;
       a.out = grad_par(n, 1 - cur, ci, p);
       a.w = wptr(n, n->aoff[l]);
-      e = launch_net_layer(a, co, ci, st);
-      if (e != hipSuccess) return e;
+      L.a[L.n++] = a;
       nnz[p] = true;
     }
+    e = launch_net_layer(L, co, ci, st);
+    if (e != hipSuccess) return e;
     gnz = nnz;
     cur = 1 - cur;
   }

@@ -15,9 +15,15 @@ struct NetLayerArgs {
   const float2* w;         // [9][COUT][CIN] complex64 weights of the layer
 };
 
-hipError_t launch_net_layer(const NetLayerArgs& a, int cin, int cout, hipStream_t st);
-hipError_t launch_net_wgrad(const NetLayerArgs& a, const float2* gy, double* partial, int cin, int cout, int nblk,
-                            hipStream_t st);
+// One launch over one or both output parities of a layer.
+struct NetLaunch {
+  NetLayerArgs a[2];
+  const float2* gy[2];     // weight gradient: output gradients on each side's parity, or null (zero field)
+  int n;                   // sides
+};
+
+hipError_t launch_net_layer(const NetLaunch& l, int cin, int cout, hipStream_t st);
+hipError_t launch_net_wgrad(const NetLaunch& l, double* partial, int cin, int cout, int nblk, hipStream_t st);
 hipError_t launch_net_wgrad_reduce(const double* partial, int cin, int cout, int nblk, int npar, double* out,
                                    hipStream_t st);
 hipError_t launch_net_embed(const void* in, float2* out, long nsites, hipStream_t st);

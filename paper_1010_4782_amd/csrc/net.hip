@@ -61,9 +61,40 @@ __device__ __forceinline__ void store_channels(float2* base, long half, long cb,
   }
 }
 
+// One side of a launch as a workgroup sees it.  The geometry stays a reference to the kernel argument: its
+// arrays are indexed by a run-time direction, which a copy would turn into scratch memory.
+struct NetView {
+  const Geo& g;
+  const char* links;
+  int out_par;
+  const float2* in_same;
+  const float2* in_other;
+  float2* out;
+  const float2* w;
+  const float2* gy;
+};
+__device__ __forceinline__ NetView net_view(const NetLaunch& l, bool second) {
+  return NetView{l.a[0].g,
+                 second ? l.a[1].links : l.a[0].links,
+                 second ? l.a[1].out_par : l.a[0].out_par,
+                 second ? l.a[1].in_same : l.a[0].in_same,
+                 second ? l.a[1].in_other : l.a[0].in_other,
+                 second ? l.a[1].out : l.a[0].out,
+                 l.a[0].w,
+                 second ? l.gy[1] : l.gy[0]};
+}
+// A layer launch: the two parities of a tile are neighbouring positions, and each XCD walks one contiguous
+// range of positions (xcd_remap), so that the activations which both sides and the neighbouring tiles read
+// are shared in that XCD's L2.
+__device__ __forceinline__ NetView net_side(const NetLaunch& l, int& tile) {
+  const int pos = xcd_remap(blockIdx.x, gridDim.x);
+  tile = l.n == 2 ? pos >> 1 : pos;
+  return net_view(l, l.n == 2 && (pos & 1));
+}
+
 // Transported colour vectors of all input channels along direction d (1..8) for the site s.
 template <int CIN>
-__device__ __forceinline__ void transported(const NetLayerArgs& a, const Site& s, long blk, int lane, int d,
+__device__ __forceinline__ void transported(const NetView& a, const Site& s, long blk, int lane, int d,
                                             Cx<float> t[CIN][3]) {
   const int mu = (d - 1) & 3;
   const bool fwd = d <= 4;
@@ -87,8 +118,10 @@ __device__ __forceinline__ void transported(const NetLayerArgs& a, const Site& s
 }
 
 template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_net_layer(NetLayerArgs a) {
-  const int cb_raw = blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void k_net_layer(NetLaunch l) {
+  int tile;
+  const NetView a = net_side(l, tile);
+  const int cb_raw = tile * blockDim.x + threadIdx.x;
   if (cb_raw >= a.g.half) return;
   const int cb = cb_raw;
   const Site s = site_of(cb, a.out_par, a.g);
@@ -141,14 +174,19 @@ __global__ __launch_bounds__(256) void k_net_layer(NetLayerArgs a) {
 // lane per site, and reach the MFMA operand layout through LDS (12 KB per wave for CIN = 8).
 //   MFMA lane layout (16x16x4): lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and
 //   C[4 (l / 16) + r][l % 16], r = 0..3.
+// At most 168 VGPRs, three waves per SIMD; left alone the compiler takes 172 and two.  Both parities of an
+// 8-channel layer at 24^3x48 take 204-217 us in one launch (272 us as two launches in launch order of the
+// sites, which read 650 MB per parity beyond L2, twice the compulsory bytes).
 template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_net_layer_mfma(NetLayerArgs a) {
+__global__ __launch_bounds__(256, 3) void k_net_layer_mfma(NetLaunch l) {
   static_assert(CIN >= 2 && CIN <= 8 && COUT >= 2 && COUT <= 8, "the matrix-core layer needs 2..8 channels");
   constexpr int KS = (CIN + 1) / 2;  // inner steps of 4 reals (2 input channels) per term
   constexpr int NT = 3 * kWave / 16;  // 16-column tiles per wave
   __shared__ float2 xs[256 / kWave][CIN][3 * kWave];
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const int cb_raw = blockIdx.x * blockDim.x + threadIdx.x;
+  int tile;
+  const NetView a = net_side(l, tile);
+  const int cb_raw = tile * blockDim.x + threadIdx.x;
   const int wave_base = cb_raw - lane;
   if (wave_base >= a.g.half) return;  // whole wave past the lattice (uniform per wave)
   const bool live = cb_raw < a.g.half;
@@ -212,14 +250,22 @@ __global__ __launch_bounds__(256) void k_net_layer_mfma(NetLayerArgs a) {
   }
 }
 
-// Weight gradient, one direction d (blockIdx.y) and a group of G output channels (blockIdx.z):
+// A workgroup of a weight-gradient launch: grid (blocks, directions or direction pairs, sides).  Block b of
+// nblk adds the sites b, b + nblk, ... (in units of a workgroup or wave); consecutive b go to one XCD
+// (xcd_remap), so that its L2 serves the neighbours, and nblk is a multiple of 8, so that the directions and
+// sides of a block share that XCD.
+__device__ __forceinline__ int wgrad_block() { return xcd_remap(blockIdx.x, gridDim.x); }
+
+// Weight gradient, one direction d (blockIdx.y), all G = C_out output channels:
 //   partial[p][d][c][c'] = sum_n sum_a G_c(n)_a conj((T_d psi_c')(n)_a)
 // over the output sites of parity a.out_par; each block walks sites with a grid stride and
 // writes one partial (complex, FP64) per (d, c, c') for a fixed-order second stage.
 template <int CIN, int COUT, int G>
-__global__ __launch_bounds__(256) void k_net_wgrad(NetLayerArgs a, const float2* gy, double* partial) {
-  const int d = blockIdx.y;
-  const int cg = blockIdx.z;
+__global__ __launch_bounds__(256) void k_net_wgrad(NetLaunch l, double* partial) {
+  const NetView a = net_view(l, blockIdx.z != 0);
+  const float2* gy = a.gy;
+  const int b = wgrad_block(), d = blockIdx.y;
+  constexpr int cg = 0;
   Cx<float> acc[G][CIN];
 #pragma unroll
   for (int c = 0; c < G; ++c)
@@ -227,7 +273,7 @@ __global__ __launch_bounds__(256) void k_net_wgrad(NetLayerArgs a, const float2*
     for (int ci = 0; ci < CIN; ++ci) acc[c][ci] = Cx<float>{0.f, 0.f};
   const bool have = d == 0 ? a.in_same != nullptr : a.in_other != nullptr;
   if (have && gy) {
-    for (int cb = blockIdx.x * blockDim.x + threadIdx.x; cb < a.g.half; cb += gridDim.x * blockDim.x) {
+    for (int cb = b * blockDim.x + threadIdx.x; cb < a.g.half; cb += gridDim.x * blockDim.x) {
       const Site s = site_of(cb, a.out_par, a.g);
       Cx<float> t[CIN][3];
       if (d == 0) {
@@ -263,7 +309,7 @@ __global__ __launch_bounds__(256) void k_net_wgrad(NetLayerArgs a, const float2*
       block_sum<2>(v, lds);
       if (threadIdx.x == 0) {
         const int co = cg * G + c;
-        const long idx = ((((long)a.out_par * 9 + d) * COUT + co) * CIN + ci) * gridDim.x + blockIdx.x;
+        const long idx = ((((long)a.out_par * 9 + d) * COUT + co) * CIN + ci) * gridDim.x + b;
         partial[2 * idx] = v[0];
         partial[2 * idx + 1] = v[1];
       }
@@ -271,72 +317,102 @@ __global__ __launch_bounds__(256) void k_net_wgrad(NetLayerArgs a, const float2*
     }
 }
 
-// Weight gradient on the matrix cores, one direction d per blockIdx.y:
+// Weight gradient on the matrix cores, two directions d per workgroup (blockIdx.y = d / 2):
 //   P[c][c'] = sum_n sum_a G_c(n)_a conj(X_d,c'(n)_a),  X_d = T_d psi (or psi for d = 0),
 // as a real GEMM over the inner index k = 2 n + part (n = 3 site + colour) with rows i = 2c + {re, im}:
 //   A[2c][(n,0)] = Re G, A[2c][(n,1)] = Im G, A[2c+1][(n,0)] = Im G, A[2c+1][(n,1)] = -Re G,
-//   B[(n,0)][c'] = Re X, B[(n,1)][c'] = Im X   (columns c' >= CIN are zero).
-// Each wave walks 64-site chunks with a grid stride and accumulates one 16x16 FP32 tile; the waves
-// of a block are summed in FP64 in a fixed order and written as one partial per block in the
-// layout of k_net_wgrad.
-constexpr int kWgradMfmaWG = 128;  // two waves: 52 KB of LDS per workgroup at 8 channels, three per CU
+//   B[(n,0)][c'] = Re X, B[(n,1)][c'] = Im X,  columns 0-7 for the first direction and 8-15 for the second
+// (unused columns are zero).  Each wave walks 64-site chunks with a grid stride and accumulates one 16x16
+// FP32 tile; the waves of a block are summed in FP64 in a fixed order and written as one partial per block
+// in the layout of k_net_wgrad.
+// G and X reach the operand layout through LDS, 32 sites at a time: 18.5 KB per wave at 8 channels, eight
+// waves per CU.  A channel's row is padded by one float2: the 8 channels that a wave reads together lie
+// 3 x 32 float2 apart, the same bank without it, and those conflicts were 60% of the launch.  Both parities
+// of an 8-channel layer at 24^3x48 take 318 us; one direction per workgroup, half the columns empty and no
+// padding took 655 us.
+constexpr int kWgradMfmaWG = 128;
 
 template <int CIN, int COUT>
-__global__ __launch_bounds__(kWgradMfmaWG) void k_net_wgrad_mfma(NetLayerArgs a, const float2* gy, double* partial) {
+__global__ __launch_bounds__(kWgradMfmaWG, 2) void k_net_wgrad_mfma(NetLaunch l, double* partial) {
   static_assert(CIN >= 2 && CIN <= 8 && COUT >= 2 && COUT <= 8, "the matrix-core gradient needs 2..8 channels");
   constexpr int NW = kWgradMfmaWG / kWave;
-  __shared__ float2 xs[NW][CIN][3 * kWave];
-  __shared__ float2 gs[NW][COUT][3 * kWave];
-  __shared__ double red[NW][kWave][4];
-  const int d = blockIdx.y;
+  constexpr int HS = kWave / 2;     // sites staged at a time
+  constexpr int RS = 3 * HS + 1;    // row stride of a staged channel, float2
+  __shared__ float2 xs[NW][2][CIN][RS];
+  __shared__ float2 gs[NW][COUT][RS];
+  double(*red)[kWave][4] = reinterpret_cast<double(*)[kWave][4]>(&xs[0][0][0][0]);  // after the last chunk
+  static_assert(sizeof(xs) >= sizeof(double) * NW * kWave * 4, "the reduction reuses the staging buffer");
+  const NetView a = net_view(l, blockIdx.z != 0);
+  const float2* gy = a.gy;
+  const int b = wgrad_block(), d0 = 2 * (int)blockIdx.y;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int row = lane & 15, kq = lane >> 4;
   f4v acc = f4v{0.f, 0.f, 0.f, 0.f};
-  const bool have = d == 0 ? a.in_same != nullptr : a.in_other != nullptr;
-  const float* xw = reinterpret_cast<const float*>(&xs[wave][0][0]);
+  const bool have0 = d0 == 0 ? a.in_same != nullptr : a.in_other != nullptr;
+  const bool have1 = d0 + 1 < 9 && a.in_other != nullptr;
   const float* gw = reinterpret_cast<const float*>(&gs[wave][0][0]);
-  if (have && gy) {
+  if ((have0 || have1) && gy) {
     const int nchunk = ceil_div(a.g.half, kWave);
-    for (int ch = blockIdx.x * NW + wave; ch < nchunk; ch += gridDim.x * NW) {  // uniform per wave
+    // operands of this lane: row c, part of G; column row & 7 of direction row >> 3 of X
+    const int c = row >> 1, ri = row & 1, part = kq & 1;
+    const int col = row & 7, dsel = row >> 3;
+    const bool bcol = col < CIN;
+    const float* xl = reinterpret_cast<const float*>(&xs[wave][dsel][bcol ? col : 0][0]) + part;
+    const float* gl = gw + (c < COUT ? c : 0) * 2 * RS + (ri == 0 ? part : 1 - part);
+    const float gsign = c < COUT ? (ri == 1 && part == 1 ? -1.f : 1.f) : 0.f;
+    for (int ch = b * NW + wave; ch < nchunk; ch += gridDim.x * NW) {  // uniform per wave
       const int cb_raw = ch * kWave + lane;
       const bool live = cb_raw < a.g.half;
       const int cb = live ? cb_raw : a.g.half - 1;
-      Cx<float> t[CIN][3];
-      if (d == 0) {
-        load_channels<CIN, CIN>(a.in_same, a.g.half, cb, 0, t);
-      } else {
-        const Site s = site_of(cb, a.out_par, a.g);
-        transported<CIN>(a, s, cb >> 6, cb & 63, d, t);
+      const Site s = site_of(cb, a.out_par, a.g);
+      Cx<float> t[2][CIN][3];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int d = d0 + q;
+        const bool have = q == 0 ? have0 : have1;
+        if (!have || !live) {
+#pragma unroll
+          for (int ci = 0; ci < CIN; ++ci)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) t[q][ci][i] = Cx<float>{0.f, 0.f};
+        } else if (d == 0) {
+          load_channels<CIN, CIN>(a.in_same, a.g.half, cb, 0, t[q]);
+        } else {
+          transported<CIN>(a, s, cb >> 6, cb & 63, d, t[q]);
+        }
       }
-#pragma unroll
-      for (int ci = 0; ci < CIN; ++ci)
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-          xs[wave][ci][3 * lane + i] = live ? make_float2(t[ci][i].re, t[ci][i].im) : make_float2(0.f, 0.f);
       Cx<float> gvs[COUT][3];
       load_channels<COUT, COUT>(gy, a.g.half, cb, 0, gvs);
+      const int ls = lane & (HS - 1);
 #pragma unroll
-      for (int c = 0; c < COUT; ++c)
+      for (int h = 0; h < 2; ++h) {
+        if ((lane >> 5) == h) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
-          gs[wave][c][3 * lane + i] = live ? make_float2(gvs[c][i].re, gvs[c][i].im) : make_float2(0.f, 0.f);
-      __builtin_amdgcn_wave_barrier();
-      // inner step ks covers n = 2 ks + (kq >> 1), part = kq & 1
-      const int c = row >> 1, ri = row & 1, part = kq & 1;
-#pragma unroll 8
-      for (int ks = 0; ks < 3 * kWave / 2; ++ks) {
-        const int n = 2 * ks + (kq >> 1);
-        float av = 0.f, bv = 0.f;
-        if (c < COUT) {
-          const float gr = gw[(c * 3 * kWave + n) * 2], gi = gw[(c * 3 * kWave + n) * 2 + 1];
-          av = ri == 0 ? (part == 0 ? gr : gi) : (part == 0 ? gi : -gr);
+          for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int ci = 0; ci < CIN; ++ci)
+#pragma unroll
+              for (int i = 0; i < 3; ++i) xs[wave][q][ci][3 * ls + i] = make_float2(t[q][ci][i].re, t[q][ci][i].im);
+#pragma unroll
+          for (int co = 0; co < COUT; ++co)
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+              gs[wave][co][3 * ls + i] = live ? make_float2(gvs[co][i].re, gvs[co][i].im) : make_float2(0.f, 0.f);
         }
-        if (row < CIN) bv = xw[(row * 3 * kWave + n) * 2 + part];
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc, 0, 0, 0);
+        __builtin_amdgcn_wave_barrier();
+        // inner step ks covers n = 2 ks + (kq >> 1), part = kq & 1
+#pragma unroll 8
+        for (int ks = 0; ks < 3 * HS / 2; ++ks) {
+          const int n = 2 * ks + (kq >> 1);
+          const float av = gsign == 0.f ? 0.f : gsign * gl[2 * n];
+          const float bv = bcol ? xl[2 * n] : 0.f;
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc, 0, 0, 0);
+        }
+        __builtin_amdgcn_wave_barrier();
       }
-      __builtin_amdgcn_wave_barrier();
     }
   }
+  __syncthreads();
 #pragma unroll
   for (int r = 0; r < 4; ++r) red[wave][lane][r] = (double)acc[r];
   __syncthreads();
@@ -347,34 +423,39 @@ __global__ __launch_bounds__(kWgradMfmaWG) void k_net_wgrad_mfma(NetLayerArgs a,
     v[r] = red[0][lane][r];
     for (int w = 1; w < NW; ++w) v[r] += red[w][lane][r];
   }
-  // C rows 4 kq + r: channel 2 kq + (r >> 1), part r & 1; column row = c'
-  const int cp = row;
-  if (cp >= CIN) return;
+  // C rows 4 kq + r: channel 2 kq + (r >> 1), part r & 1; column row: c' = row & 7 of direction d0 + (row >> 3)
+  const int cp = row & 7, d = d0 + (row >> 3);
+  if (cp >= CIN || d >= 9) return;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int co = 2 * kq + h;
     if (co >= COUT) continue;
-    const long idx = ((((long)a.out_par * 9 + d) * COUT + co) * CIN + cp) * gridDim.x + blockIdx.x;
+    const long idx = ((((long)a.out_par * 9 + d) * COUT + co) * CIN + cp) * gridDim.x + b;
     partial[2 * idx] = v[2 * h];
     partial[2 * idx + 1] = v[2 * h + 1];
   }
 }
 
-// out[d][c][c'] = sum over parities and blocks of the partials, in a fixed order.
-__global__ __launch_bounds__(64) void k_net_wgrad_reduce(const double* partial, int cin, int cout, int nblk,
-                                                         int npar, double* out) {  // out += sum
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;  // (d, c, c') flat
-  const int n = 9 * cout * cin;
-  if (j >= n) return;
-  double re = 0.0, im = 0.0;
-  for (int p = 0; p < npar; ++p)
-    for (int b = 0; b < nblk; ++b) {
-      const long idx = ((long)p * n + j) * nblk + b;
-      re += partial[2 * idx];
-      im += partial[2 * idx + 1];
-    }
-  out[2 * j] += re;
-  out[2 * j + 1] += im;
+// out[d][c][c'] += sum over parities and blocks of the partials, in a fixed order.  One wave per (d, c, c'):
+// the partials of one parity and output are contiguous and go through LDS, so that the serial sum waits on
+// LDS and not on memory (one lane walking them in memory took 60 us of dependent loads, this 5).
+constexpr int kWgradReduceMax = 512;
+__global__ __launch_bounds__(64) void k_net_wgrad_reduce(const double* partial, int n, int nblk, int npar,
+                                                         double* out) {
+  __shared__ double2 s[kWgradReduceMax];
+  const int j = blockIdx.x;  // (d, c, c') flat, of n
+  const double2* src = reinterpret_cast<const double2*>(partial);
+  for (int i = threadIdx.x; i < npar * nblk; i += kWave) {
+    const int p = i / nblk;
+    s[i] = src[((long)p * n + j) * nblk + (i - p * nblk)];
+  }
+  __syncthreads();
+  if (threadIdx.x > 1) return;
+  const double* v = reinterpret_cast<const double*>(s) + threadIdx.x;  // lane 0 real, lane 1 imaginary parts
+  double sum = 0.0;
+#pragma unroll 16
+  for (int i = 0; i < npar * nblk; ++i) sum += v[2 * i];
+  out[2 * j + threadIdx.x] += sum;
 }
 
 // even-site complex128 vector -> channel 0 of a complex64 activation (parity 0)
@@ -419,14 +500,15 @@ __global__ __launch_bounds__(256) void k_sum_partials(const double* partial, int
 }
 
 // ---- launchers ---------------------------------------------------------------------
-hipError_t launch_net_layer(const NetLayerArgs& a, int cin, int cout, hipStream_t st) {
-  const int nb = ceil_div(a.g.half, 256);
+hipError_t launch_net_layer(const NetLaunch& l, int cin, int cout, hipStream_t st) {
+  if (l.n == 0) return hipSuccess;
+  const int nb = ceil_div(l.a[0].g.half, 256) * l.n;
   // layers with at least two channels on both sides mix on the matrix cores; 1 -> C and C -> 1
   // would fill at most a quarter of an MFMA tile and stay on the vector units
 #define STAG_NET_LAYER(I, O) \
-  if (cin == I && cout == O) { k_net_layer<I, O><<<nb, 256, 0, st>>>(a); return hipGetLastError(); }
+  if (cin == I && cout == O) { k_net_layer<I, O><<<nb, 256, 0, st>>>(l); return hipGetLastError(); }
 #define STAG_NET_LAYER_MFMA(I, O) \
-  if (cin == I && cout == O) { k_net_layer_mfma<I, O><<<nb, 256, 0, st>>>(a); return hipGetLastError(); }
+  if (cin == I && cout == O) { k_net_layer_mfma<I, O><<<nb, 256, 0, st>>>(l); return hipGetLastError(); }
   STAG_NET_LAYER(1, 1) STAG_NET_LAYER(1, 2) STAG_NET_LAYER(2, 1) STAG_NET_LAYER_MFMA(2, 2)
   STAG_NET_LAYER(1, 4) STAG_NET_LAYER(4, 1) STAG_NET_LAYER_MFMA(4, 4)
   STAG_NET_LAYER(1, 8) STAG_NET_LAYER(8, 1) STAG_NET_LAYER_MFMA(8, 8)
@@ -435,21 +517,20 @@ hipError_t launch_net_layer(const NetLayerArgs& a, int cin, int cout, hipStream_
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_net_wgrad(const NetLayerArgs& a, const float2* gy, double* partial, int cin, int cout, int nblk,
-                            hipStream_t st) {
-#define STAG_NET_WG(I, O, G)                                                  \
-  if (cin == I && cout == O) {                                                \
-    k_net_wgrad<I, O, G><<<dim3(nblk, 9, O / G), 256, 0, st>>>(a, gy, partial); \
-    return hipGetLastError();                                                 \
+hipError_t launch_net_wgrad(const NetLaunch& l, double* partial, int cin, int cout, int nblk, hipStream_t st) {
+#define STAG_NET_WG(I, O)                                                          \
+  if (cin == I && cout == O) {                                                     \
+    k_net_wgrad<I, O, O><<<dim3(nblk, 9, l.n), 256, 0, st>>>(l, partial);          \
+    return hipGetLastError();                                                      \
   }
-#define STAG_NET_WG_MFMA(I, O)                                                       \
-  if (cin == I && cout == O) {                                                       \
-    k_net_wgrad_mfma<I, O><<<dim3(nblk, 9, 1), kWgradMfmaWG, 0, st>>>(a, gy, partial); \
-    return hipGetLastError();                                                        \
+#define STAG_NET_WG_MFMA(I, O)                                                     \
+  if (cin == I && cout == O) {                                                     \
+    k_net_wgrad_mfma<I, O><<<dim3(nblk, 5, l.n), kWgradMfmaWG, 0, st>>>(l, partial); \
+    return hipGetLastError();                                                      \
   }
-  STAG_NET_WG(1, 1, 1) STAG_NET_WG(1, 2, 2) STAG_NET_WG(2, 1, 1) STAG_NET_WG_MFMA(2, 2)
-  STAG_NET_WG(1, 4, 4) STAG_NET_WG(4, 1, 1) STAG_NET_WG_MFMA(4, 4)
-  STAG_NET_WG(1, 8, 8) STAG_NET_WG(8, 1, 1) STAG_NET_WG_MFMA(8, 8)
+  STAG_NET_WG(1, 1) STAG_NET_WG(1, 2) STAG_NET_WG(2, 1) STAG_NET_WG_MFMA(2, 2)
+  STAG_NET_WG(1, 4) STAG_NET_WG(4, 1) STAG_NET_WG_MFMA(4, 4)
+  STAG_NET_WG(1, 8) STAG_NET_WG(8, 1) STAG_NET_WG_MFMA(8, 8)
 #undef STAG_NET_WG
 #undef STAG_NET_WG_MFMA
   return hipErrorInvalidValue;
@@ -457,8 +538,9 @@ hipError_t launch_net_wgrad(const NetLayerArgs& a, const float2* gy, double* par
 
 hipError_t launch_net_wgrad_reduce(const double* partial, int cin, int cout, int nblk, int npar, double* out,
                                    hipStream_t st) {
+  if (npar * nblk > kWgradReduceMax) return hipErrorInvalidValue;
   const int n = 9 * cout * cin;
-  k_net_wgrad_reduce<<<ceil_div(n, 64), 64, 0, st>>>(partial, cin, cout, nblk, npar, out);
+  k_net_wgrad_reduce<<<n, kWave, 0, st>>>(partial, n, nblk, npar, out);
   return hipGetLastError();
 }
 
