@@ -35,6 +35,17 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
   return xcd < r ? xcd * (q + 1) + idx : r * (q + 1) + (xcd - r) * q + idx;
 }
 
+// The same with a sweep: XCD `xcd` takes the positions [xcd S / 8, (xcd + 1) S / 8) of every time slice of S
+// sites and walks t through them, so that a site's t neighbours are read by the same XCD an eighth of a slice
+// apart.  Site of the XCD's i-th lane position, or -1 past its end; xcd_sweep_len positions per XCD at most.
+__device__ __forceinline__ int xcd_sweep_site(int xcd, int i, int S, int lt) {
+  const int s0 = (int)((long)xcd * S >> 3), len = (int)((long)(xcd + 1) * S >> 3) - s0;
+  if (len == 0) return -1;
+  const int t = i / len;
+  return t < lt ? t * S + s0 + (i - t * len) : -1;
+}
+inline long xcd_sweep_len(int S, int lt) { return (long)((S + 7) / 8) * lt; }
+
 // ---- binary16 helpers -------------------------------------------------------
 typedef _Float16 h2v __attribute__((ext_vector_type(2)));
 

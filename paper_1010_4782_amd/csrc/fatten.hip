@@ -29,6 +29,7 @@
 // field take 3.9 ms; 110 launches over matrices in the user layout, one wrap each, took 16.6 ms.
 #include <hip/hip_runtime.h>
 
+#include "device.h"
 #include "fatten.h"
 
 namespace stag {
@@ -139,22 +140,12 @@ __device__ __forceinline__ M3 mul(const M3& a, const M3& b) {
 
 constexpr int kFatWG = 256;
 
-// Workgroups go round-robin over the 8 XCDs, and each XCD has its own L2.  XCD x takes the z planes
-// [x Lz / 8, (x + 1) Lz / 8) and sweeps t through them, so that a site's t neighbours are read by the same
-// XCD a few thousand sites apart and are still in its L2.
-__device__ __forceinline__ int zblock(const FGeo& g, int x) { return x * g.L[2] / 8; }
-// The site of this lane, or -1 past the end of the XCD's block.
+// The site of this lane in XCD-sweep order (xcd_sweep_site), or -1: workgroups go round-robin over the XCDs.
 __device__ __forceinline__ int my_site(const FGeo& g) {
-  const int x = blockIdx.x & 7, i = (int)(blockIdx.x >> 3) * kFatWG + threadIdx.x;
-  const int z0 = zblock(g, x), per_t = (zblock(g, x + 1) - z0) * g.stride[2];
-  if (per_t == 0) return -1;
-  const int t = i / per_t;
-  if (t >= g.L[3]) return -1;
-  return t * g.stride[3] + z0 * g.stride[2] + (i - t * per_t);
+  return xcd_sweep_site(blockIdx.x & 7, (int)(blockIdx.x >> 3) * kFatWG + threadIdx.x, g.stride[3], g.L[3]);
 }
 inline int site_blocks(const FGeo& g) {
-  const int zmax = (g.L[2] + 7) / 8;
-  return 8 * (int)(((long)zmax * g.stride[2] * g.L[3] + kFatWG - 1) / kFatWG);
+  return 8 * (int)((xcd_sweep_len(g.stride[3], g.L[3]) + kFatWG - 1) / kFatWG);
 }
 
 // The k-th transverse direction of mu, k = 0..2

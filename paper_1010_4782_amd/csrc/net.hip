@@ -8,10 +8,10 @@
 // k = 4 mu + 1 is -F~_mu(n-mu)^dag, so T_{-mu} = -L_{4mu+1}.
 //
 // Activations are complex64, stored per parity.  With C >= 2 channels they are interleaved in
-// channel pairs, [parity][C/2][V/2][3 colours][2 channels] (48 B per pair and site, three 16-byte
-// loads), so that reading all channels of a neighbour takes 3C/2 wide loads instead of 3C narrow
-// ones; a single channel is [parity][V/2][3].  A null input pointer stands for a field that is
-// zero on that parity.
+// channel pairs, [parity][C/2][3 colours][V/2][2 channels], so that reading all channels of a
+// neighbour takes 3C/2 16-byte loads, each 1 KiB contiguous over a wave (with the colours of a site next
+// to each other it spread over 3 KiB, and the load units set the pace of the layers); a single channel is
+// [parity][3][V/2].  A null input pointer stands for a field that is zero on that parity.
 #include "device.h"
 #include "net.h"
 #include "launch.h"
@@ -29,15 +29,20 @@ __device__ __forceinline__ void cmac_f(Cx<float>& acc, const float2 w, const Cx<
 template <int C, int G>
 __device__ __forceinline__ void load_channels(const float2* base, long half, long cb, int c0, Cx<float> t[G][3]) {
   if constexpr (C == 1) {
-    load_spinor<P32>(base, cb, t[0]);
+    gptr<f2v> p = as_global<f2v>(base) + cb;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const f2v w = p[i * half];
+      t[0][i] = Cx<float>{w.x, w.y};
+    }
   } else {
     static_assert(G % 2 == 0, "channel pairs are loaded whole");
 #pragma unroll
     for (int q = 0; q < G / 2; ++q) {
-      gptr<f4v> p = as_global<f4v>(base + ((long)(c0 / 2 + q) * half + cb) * 6);
+      gptr<f4v> p = as_global<f4v>(base) + (long)(c0 / 2 + q) * 3 * half + cb;
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        const f4v w = p[i];
+        const f4v w = p[i * half];
         t[2 * q][i] = Cx<float>{w.x, w.y};
         t[2 * q + 1][i] = Cx<float>{w.z, w.w};
       }
@@ -48,15 +53,16 @@ __device__ __forceinline__ void load_channels(const float2* base, long half, lon
 template <int C>
 __device__ __forceinline__ void store_channels(float2* base, long half, long cb, const Cx<float> v[C][3]) {
   if constexpr (C == 1) {
-    gptr_w<f2v> p = as_global_w<f2v>(base + cb * 3);
+    gptr_w<f2v> p = as_global_w<f2v>(base) + cb;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) p[i] = f2v{v[0][i].re, v[0][i].im};
+    for (int i = 0; i < 3; ++i) p[i * half] = f2v{v[0][i].re, v[0][i].im};
   } else {
 #pragma unroll
     for (int q = 0; q < C / 2; ++q) {
-      gptr_w<f4v> p = as_global_w<f4v>(base + ((long)q * half + cb) * 6);
+      gptr_w<f4v> p = as_global_w<f4v>(base) + (long)q * 3 * half + cb;
 #pragma unroll
-      for (int i = 0; i < 3; ++i) p[i] = f4v{v[2 * q][i].re, v[2 * q][i].im, v[2 * q + 1][i].re, v[2 * q + 1][i].im};
+      for (int i = 0; i < 3; ++i)
+        p[i * half] = f4v{v[2 * q][i].re, v[2 * q][i].im, v[2 * q + 1][i].re, v[2 * q + 1][i].im};
     }
   }
 }
@@ -83,13 +89,13 @@ __device__ __forceinline__ NetView net_view(const NetLaunch& l, bool second) {
                  l.a[0].w,
                  second ? l.gy[1] : l.gy[0]};
 }
-// A layer launch: the two parities of a tile are neighbouring positions, and each XCD walks one contiguous
-// range of positions (xcd_remap), so that the activations which both sides and the neighbouring tiles read
-// are shared in that XCD's L2.
-__device__ __forceinline__ NetView net_side(const NetLaunch& l, int& tile) {
-  const int pos = xcd_remap(blockIdx.x, gridDim.x);
-  tile = l.n == 2 ? pos >> 1 : pos;
-  return net_view(l, l.n == 2 && (pos & 1));
+// A layer launch: workgroups in XCD-sweep order (xcd_sweep_site), the two parities of a tile next to each
+// other, so that the activations which both sides and the neighbouring sites read are shared in an XCD's L2.
+__device__ __forceinline__ NetView net_side(const NetLaunch& l, int& cb) {
+  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+  const Geo& g = l.a[0].g;
+  cb = xcd_sweep_site(xcd, (l.n == 2 ? j >> 1 : j) * blockDim.x + threadIdx.x, g.stride[3], g.L[3]);
+  return net_view(l, l.n == 2 && (j & 1));
 }
 
 // Transported colour vectors of all input channels along direction d (1..8) for the site s.
@@ -119,11 +125,9 @@ __device__ __forceinline__ void transported(const NetView& a, const Site& s, lon
 
 template <int CIN, int COUT>
 __global__ __launch_bounds__(256) void k_net_layer(NetLaunch l) {
-  int tile;
-  const NetView a = net_side(l, tile);
-  const int cb_raw = tile * blockDim.x + threadIdx.x;
-  if (cb_raw >= a.g.half) return;
-  const int cb = cb_raw;
+  int cb;
+  const NetView a = net_side(l, cb);
+  if (cb < 0) return;
   const Site s = site_of(cb, a.out_par, a.g);
   const long blk = cb >> 6;
   const int lane = cb & 63;
@@ -166,105 +170,158 @@ __global__ __launch_bounds__(256) void k_net_layer(NetLaunch l) {
 
 // Channel mixing on the matrix cores.  For the 64 sites of one wave and one term d (identity or a
 // transport), the mixing is the complex product Y[c][n] += sum_c' W_d[c][c'] X_d[c'][n] over the
-// 192 columns n = 3 site + colour.  It runs as a real GEMM with the 2x2 real form of each complex
+// 192 columns n = (site, colour).  It runs as a real GEMM with the 2x2 real form of each complex
 // weight: rows i = 2c + {re, im}, inner index k = 2c' + {re, im},
 //   A[2c][2c'] = Re W, A[2c][2c'+1] = -Im W, A[2c+1][2c'] = Im W, A[2c+1][2c'+1] = Re W,
-// on v_mfma_f32_16x16x4_f32 (A 16x4, B 4x16, C 16x16 in FP32): twelve 16-column tiles, and
-// ceil(CIN/2) steps of 4 inner indices per term.  The transports stay on the vector units, one
-// lane per site, and reach the MFMA operand layout through LDS (12 KB per wave for CIN = 8).
+// on v_mfma_f32_16x16x4_f32 (A 16x4, B 4x16, C 16x16 in FP32): twelve 16-column tiles (colour i, lanes
+// 16 q .. 16 q + 15), and ceil(CIN/2) steps of 4 inner indices per term.
 //   MFMA lane layout (16x16x4): lane l holds A[l % 16][l / 16], B[l / 16][l % 16] and
 //   C[4 (l / 16) + r][l % 16], r = 0..3.
-// At most 168 VGPRs, three waves per SIMD; left alone the compiler takes 172 and two.  Both parities of an
-// 8-channel layer at 24^3x48 take 204-217 us in one launch (272 us as two launches in launch order of the
-// sites, which read 650 MB per parity beyond L2, twice the compulsory bytes).
+// The transports stay on the vector units, one lane per site.  FP32 products on the matrix cores do not
+// overlap other vector instructions, so the two add up (about 24 thousand cycles per wave at 8 channels) and
+// bound the kernel; the rest has to stay out of their way.  One stage is one channel pair of one term: its
+// four components go to the operand layout through LDS (12 four-byte writes, 3 sixteen-byte reads, free of
+// bank conflicts) while the products of the stage before run, and the pair's registers take the loads of
+// the next term at once.  Both parities of an 8-channel layer at 24^3x48 take 197 us (145 us with every load
+// left out, 82 us without the products too); two launches in launch order of the sites, whose operand reads
+// waited out an LDS latency for each pair of products, took 272 us.
 template <int CIN, int COUT>
-__global__ __launch_bounds__(256, 3) void k_net_layer_mfma(NetLaunch l) {
-  static_assert(CIN >= 2 && CIN <= 8 && COUT >= 2 && COUT <= 8, "the matrix-core layer needs 2..8 channels");
-  constexpr int KS = (CIN + 1) / 2;  // inner steps of 4 reals (2 input channels) per term
-  constexpr int NT = 3 * kWave / 16;  // 16-column tiles per wave
-  __shared__ float2 xs[256 / kWave][CIN][3 * kWave];
+__global__ __launch_bounds__(256, 2) void k_net_layer_mfma(NetLaunch l) {
+  static_assert(CIN >= 2 && CIN <= 8 && CIN % 2 == 0, "the matrix-core layer takes channel pairs, at most 4");
+  static_assert(COUT >= 2 && COUT <= 8 && COUT % 2 == 0, "matrix-core layers write whole channel pairs");
+  constexpr int KS = CIN / 2;  // inner steps of 4 reals (2 input channels) per term
+  __shared__ __align__(16) float xs[256 / kWave][2][kWave * 12];
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  int tile;
-  const NetView a = net_side(l, tile);
-  const int cb_raw = tile * blockDim.x + threadIdx.x;
-  const int wave_base = cb_raw - lane;
-  if (wave_base >= a.g.half) return;  // whole wave past the lattice (uniform per wave)
-  const bool live = cb_raw < a.g.half;
-  const int cb = live ? cb_raw : a.g.half - 1;  // dead lanes compute a valid site; their columns are not stored
+  int own;
+  const NetView a = net_side(l, own);
+  if (__ballot(own >= 0) == 0) return;  // the whole wave is past the lattice
+  const int cb = own >= 0 ? own : 0;  // dead lanes compute a valid site; their columns are not stored
   const Site s = site_of(cb, a.out_par, a.g);
+  const long half = a.g.half;
   const int row = lane & 15, kq = lane >> 4;
-  f4v acc[NT];
+  f4v acc[3][4];
 #pragma unroll
-  for (int j = 0; j < NT; ++j) acc[j] = f4v{0.f, 0.f, 0.f, 0.f};
-  float* xw = reinterpret_cast<float*>(&xs[wave][0][0]);
-#pragma unroll 1
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[i][q] = f4v{0.f, 0.f, 0.f, 0.f};
+  // A operand of this lane: row `row` (channel c, part ri), inner index 4 ks + kq (channel 2 ks + kq / 2, part ki)
+  const int c = row >> 1, ri = row & 1, ki = kq & 1;
+  const float* wl = reinterpret_cast<const float*>(a.w) + 2 * ((c < COUT ? c : 0) * CIN + (kq >> 1)) + (ri ^ ki);
+  auto load_weights = [&](int d, float w[KS]) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) w[ks] = c < COUT ? wl[2 * (d * COUT * CIN + 2 * ks)] : 0.f;
+  };
+  auto load_u = [&](int d, Cx<float> u[9]) {
+    const int k = 4 * ((d - 1) & 3) + (d <= 4 ? 0 : 1);
+    if (a.g.long12)
+      load_link<P32, true>(a.links, cb >> 6, k, cb & 63, 1.f, u);
+    else
+      load_link<P32, false>(a.links, cb >> 6, k, cb & 63, 1.f, u);
+  };
+  auto source = [&](int d) {  // the site whose channels term d reads
+    return d == 0 ? cb : neighbour(s, a.g, (d - 1) & 3, a.g.h1[(d - 1) & 3], d <= 4);
+  };
+  Cx<float> v[KS][2][3], u[2][9];
+  float w[3][KS];
+  load_weights(0, w[0]);
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) load_channels<CIN, 2>(a.in_same, half, cb, 2 * ks, v[ks]);
+  float* xw = xs[wave][0];
+  const int wr = 12 * row + kq;            // this lane as the site 16 kq + row: [part of k][row][colour][q]
+  const int rd = (kq * 16 + row) * 12;     // ... and as an operand lane
+  f4v bv[3];
+#pragma unroll
   for (int d = 0; d < 9; ++d) {
-    if (d == 0 ? a.in_same == nullptr : a.in_other == nullptr) continue;  // uniform
-    Cx<float> t[CIN][3];
-    if (d == 0) {
-      load_channels<CIN, CIN>(a.in_same, a.g.half, cb, 0, t);
-    } else {
-      transported<CIN>(a, s, cb >> 6, cb & 63, d, t);
+    int nb = 0;
+    if (d < 8) {
+      nb = source(d + 1);
+      load_weights(d + 1, w[(d + 1) % 3]);
+      load_u(d + 1, u[(d + 1) & 1]);
     }
+    if (d > 4)
 #pragma unroll
-    for (int ci = 0; ci < CIN; ++ci)
-#pragma unroll
-      for (int i = 0; i < 3; ++i) xs[wave][ci][3 * lane + i] = make_float2(t[ci][i].re, t[ci][i].im);
-    __builtin_amdgcn_wave_barrier();
-    // A operand of this lane: row `row`, inner index 4 ks + kq
-    float av[KS];
-    {
-      const int c = row >> 1, ri = row & 1;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const int k = 4 * ks + kq, cp = k >> 1, ki = k & 1;
-        float v = 0.f;
-        if (c < COUT && cp < CIN) {
-          const float2 w = a.w[(d * COUT + c) * CIN + cp];
-          v = ri == 0 ? (ki == 0 ? w.x : -w.y) : (ki == 0 ? w.y : w.x);
-        }
-        av[ks] = v;
-      }
-    }
+      for (int e = 0; e < 9; ++e) u[d & 1][e] = Cx<float>{-u[d & 1][e].re, -u[d & 1][e].im};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      const int cp = 2 * ks + (kq >> 1), ki = kq & 1;
+      Cx<float> t[2][3];
 #pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const float bv = cp < CIN ? xw[(cp * 3 * kWave + 16 * j + row) * 2 + ki] : 0.f;
-        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ks], bv, acc[j], 0, 0, 0);
+      for (int h = 0; h < 2; ++h) {
+        if (d == 0) {
+#pragma unroll
+          for (int i = 0; i < 3; ++i) t[h][i] = v[ks][h][i];
+        } else {
+#pragma unroll
+          for (int i = 0; i < 3; ++i) t[h][i] = Cx<float>{0.f, 0.f};
+          matvec_acc(u[d & 1], v[ks][h], t[h]);
+        }
       }
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-  // C rows 4 kq .. 4 kq + 3 are channels 2 kq and 2 kq + 1, (re, im) each; column 16 j + row.
-  static_assert(COUT % 2 == 0, "matrix-core layers write whole channel pairs");
-  const int c0 = 2 * kq;
+      if (d < 8) load_channels<CIN, 2>(a.in_other, half, nb, 2 * ks, v[ks]);
+      const int stage = d * KS + ks;
+      float* x = xw + (stage & 1) * (kWave * 12);
 #pragma unroll
-  for (int j = 0; j < NT; ++j) {
-    const int n = 16 * j + row;
-    const int site = wave_base + n / 3, colour = n % 3;
-    if (site >= a.g.half || c0 >= COUT) continue;
-    // channels c0, c0 + 1 are one pair of the interleaved layout: one 16-byte store
-    as_global_w<f4v>(a.out + ((long)kq * a.g.half + site) * 6)[colour] = acc[j];
+      for (int i = 0; i < 3; ++i) {
+        x[wr + 4 * i] = t[0][i].re;
+        x[wr + 4 * i + 192] = t[0][i].im;
+        x[wr + 4 * i + 384] = t[1][i].re;
+        x[wr + 4 * i + 576] = t[1][i].im;
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (stage > 0) {
+        const int pd = ks ? d : d - 1, pk = ks ? ks - 1 : KS - 1;  // the stage before
+        const float av = ri == 0 && ki == 1 ? -w[pd % 3][pk] : w[pd % 3][pk];
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[i][q], acc[i][q], 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 3; ++i) bv[i] = *reinterpret_cast<const f4v*>(x + rd + 4 * i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  {
+    const float av = ri == 0 && ki == 1 ? -w[8 % 3][KS - 1] : w[8 % 3][KS - 1];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[i][q], acc[i][q], 0, 0, 0);
+  }
+  // C rows 4 kq .. 4 kq + 3 are channels 2 kq and 2 kq + 1, (re, im) each: one pair of the interleaved layout
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int site = __shfl(own, 16 * q + row, kWave);
+    if (site < 0 || 2 * kq >= COUT) continue;
+    gptr_w<f4v> o = as_global_w<f4v>(a.out) + (long)kq * 3 * half + site;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) o[(long)i * half] = acc[i][q];
   }
 }
 
-// A workgroup of a weight-gradient launch: grid (blocks, directions or direction pairs, sides).  Block b of
-// nblk adds the sites b, b + nblk, ... (in units of a workgroup or wave); consecutive b go to one XCD
-// (xcd_remap), so that its L2 serves the neighbours, and nblk is a multiple of 8, so that the directions and
-// sides of a block share that XCD.
-__device__ __forceinline__ int wgrad_block() { return xcd_remap(blockIdx.x, gridDim.x); }
+// A workgroup of a weight-gradient launch: block b of nblk adds the sites b, b + nblk, ... (in units of a
+// workgroup or wave), for one of nd directions (or pairs) and one side.  Eight consecutive workgroups go to
+// the eight XCDs; on each, the directions and sides of one block follow each other and run together, reading
+// the same output gradients and neighbourhood through one L2, and consecutive blocks stay on one XCD.
+// nblk is a multiple of 8.
+struct WgradBlock {
+  int b, d, side;
+};
+__device__ __forceinline__ WgradBlock wgrad_block(int nblk, int nd, int nside) {
+  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3, per = nd * nside, k = j % per;
+  return WgradBlock{xcd * (nblk >> 3) + j / per, k % nd, k / nd};
+}
 
 // Weight gradient, one direction d (blockIdx.y), all G = C_out output channels:
 //   partial[p][d][c][c'] = sum_n sum_a G_c(n)_a conj((T_d psi_c')(n)_a)
 // over the output sites of parity a.out_par; each block walks sites with a grid stride and
 // writes one partial (complex, FP64) per (d, c, c') for a fixed-order second stage.
 template <int CIN, int COUT, int G>
-__global__ __launch_bounds__(256) void k_net_wgrad(NetLaunch l, double* partial) {
-  const NetView a = net_view(l, blockIdx.z != 0);
+__global__ __launch_bounds__(256) void k_net_wgrad(NetLaunch l, double* partial, int nblk) {
+  const WgradBlock wb = wgrad_block(nblk, 9, l.n);
+  const NetView a = net_view(l, wb.side != 0);
   const float2* gy = a.gy;
-  const int b = wgrad_block(), d = blockIdx.y;
+  const int b = wb.b, d = wb.d;
   constexpr int cg = 0;
   Cx<float> acc[G][CIN];
 #pragma unroll
@@ -273,7 +330,7 @@ __global__ __launch_bounds__(256) void k_net_wgrad(NetLaunch l, double* partial)
     for (int ci = 0; ci < CIN; ++ci) acc[c][ci] = Cx<float>{0.f, 0.f};
   const bool have = d == 0 ? a.in_same != nullptr : a.in_other != nullptr;
   if (have && gy) {
-    for (int cb = b * blockDim.x + threadIdx.x; cb < a.g.half; cb += gridDim.x * blockDim.x) {
+    for (int cb = b * blockDim.x + threadIdx.x; cb < a.g.half; cb += nblk * blockDim.x) {
       const Site s = site_of(cb, a.out_par, a.g);
       Cx<float> t[CIN][3];
       if (d == 0) {
@@ -309,7 +366,7 @@ __global__ __launch_bounds__(256) void k_net_wgrad(NetLaunch l, double* partial)
       block_sum<2>(v, lds);
       if (threadIdx.x == 0) {
         const int co = cg * G + c;
-        const long idx = ((((long)a.out_par * 9 + d) * COUT + co) * CIN + ci) * gridDim.x + b;
+        const long idx = ((((long)a.out_par * 9 + d) * COUT + co) * CIN + ci) * nblk + b;
         partial[2 * idx] = v[0];
         partial[2 * idx + 1] = v[1];
       }
@@ -325,91 +382,114 @@ __global__ __launch_bounds__(256) void k_net_wgrad(NetLaunch l, double* partial)
 // (unused columns are zero).  Each wave walks 64-site chunks with a grid stride and accumulates one 16x16
 // FP32 tile; the waves of a block are summed in FP64 in a fixed order and written as one partial per block
 // in the layout of k_net_wgrad.
-// G and X reach the operand layout through LDS, 32 sites at a time: 18.5 KB per wave at 8 channels, eight
-// waves per CU.  A channel's row is padded by one float2: the 8 channels that a wave reads together lie
-// 3 x 32 float2 apart, the same bank without it, and those conflicts were 60% of the launch.  Both parities
-// of an 8-channel layer at 24^3x48 take 318 us; one direction per workgroup, half the columns empty and no
-// padding took 655 us.
+// Half a wave works on each direction, 32 sites at a time, and on half of the output channels.  G and X reach
+// the operand layout through LDS (18.8 KB per wave at 8 channels, eight waves per CU), stored as
+// [channel][k of the step][step], so that a lane reads the operands of four consecutive steps with one
+// 16-byte load.  Row strides of 196 floats spread the 16 rows over the banks; the rows were 384 floats apart
+// before, all on one bank, and those conflicts were 60% of the launch.  The loads of the next 32 sites are in
+// flight during the products.  Both parities of an 8-channel layer at 24^3x48 take 276 us; with one direction
+// per workgroup, half the columns empty, 655 us.
 constexpr int kWgradMfmaWG = 128;
 
 template <int CIN, int COUT>
-__global__ __launch_bounds__(kWgradMfmaWG, 2) void k_net_wgrad_mfma(NetLaunch l, double* partial) {
+__global__ __launch_bounds__(kWgradMfmaWG, 2) void k_net_wgrad_mfma(NetLaunch l, double* partial, int nblk) {
   static_assert(CIN >= 2 && CIN <= 8 && COUT >= 2 && COUT <= 8, "the matrix-core gradient needs 2..8 channels");
   constexpr int NW = kWgradMfmaWG / kWave;
-  constexpr int HS = kWave / 2;     // sites staged at a time
-  constexpr int RS = 3 * HS + 1;    // row stride of a staged channel, float2
-  __shared__ float2 xs[NW][2][CIN][RS];
-  __shared__ float2 gs[NW][COUT][RS];
+  constexpr int HS = kWave / 2;        // sites staged at a time
+  constexpr int NS = 3 * HS / 2;       // inner steps of 4 (two n, both parts) they make
+  constexpr int RS = 4 * NS + 4;       // row stride of a staged channel
+  __shared__ __align__(16) float xs[NW][2][CIN][RS];
+  __shared__ __align__(16) float gs[NW][COUT][RS];
   double(*red)[kWave][4] = reinterpret_cast<double(*)[kWave][4]>(&xs[0][0][0][0]);  // after the last chunk
   static_assert(sizeof(xs) >= sizeof(double) * NW * kWave * 4, "the reduction reuses the staging buffer");
-  const NetView a = net_view(l, blockIdx.z != 0);
+  const WgradBlock wb = wgrad_block(nblk, 5, l.n);
+  const NetView a = net_view(l, wb.side != 0);
   const float2* gy = a.gy;
-  const int b = wgrad_block(), d0 = 2 * (int)blockIdx.y;
+  const int b = wb.b, d0 = 2 * wb.d;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const int row = lane & 15, kq = lane >> 4;
   f4v acc = f4v{0.f, 0.f, 0.f, 0.f};
-  const bool have0 = d0 == 0 ? a.in_same != nullptr : a.in_other != nullptr;
-  const bool have1 = d0 + 1 < 9 && a.in_other != nullptr;
-  const float* gw = reinterpret_cast<const float*>(&gs[wave][0][0]);
-  if ((have0 || have1) && gy) {
-    const int nchunk = ceil_div(a.g.half, kWave);
-    // operands of this lane: row c, part of G; column row & 7 of direction row >> 3 of X
-    const int c = row >> 1, ri = row & 1, part = kq & 1;
-    const int col = row & 7, dsel = row >> 3;
-    const bool bcol = col < CIN;
-    const float* xl = reinterpret_cast<const float*>(&xs[wave][dsel][bcol ? col : 0][0]) + part;
-    const float* gl = gw + (c < COUT ? c : 0) * 2 * RS + (ri == 0 ? part : 1 - part);
-    const float gsign = c < COUT ? (ri == 1 && part == 1 ? -1.f : 1.f) : 0.f;
-    for (int ch = b * NW + wave; ch < nchunk; ch += gridDim.x * NW) {  // uniform per wave
-      const int cb_raw = ch * kWave + lane;
-      const bool live = cb_raw < a.g.half;
-      const int cb = live ? cb_raw : a.g.half - 1;
+  if (gy) {
+    const int nhalf = ceil_div(a.g.half, kWave) * 2;  // 32-site halves of the chunks
+    // operands of this lane: row c, part ri of G; column row & 7 of direction row >> 3 of X
+    const int c = row >> 1, ri = row & 1;
+    const bool bcol = (row & 7) < CIN;
+    const float* xl = &xs[wave][row >> 3][bcol ? row & 7 : 0][kq * NS];
+    const float* gl = &gs[wave][c < COUT ? c : 0][(kq ^ ri) * NS];
+    const float gsign = c < COUT ? (ri == 1 && (kq & 1) == 1 ? -1.f : 1.f) : 0.f;
+    // what this lane loads: direction d0 + q, and GC channels of G from gc0 on (with two channels both halves
+    // load the pair and each stages one)
+    constexpr int GC = COUT >= 4 ? COUT / 2 : 2;
+    const int q = lane >> 5, ls = lane & (HS - 1), d = d0 + q, gc0 = COUT >= 4 ? q * GC : 0;
+    const int mu0 = (d0 - 1) & 3, mu1 = d0 & 3;
+    const int k = q ? 4 * mu1 + (d0 + 1 <= 4 ? 0 : 1) : 4 * mu0 + (d0 <= 4 ? 0 : 1);
+    Cx<float> u[9], v[CIN][3], gvs[GC][3];
+    auto load_half = [&](int hc) {  // sites 32 hc ..
+      const int cb = min(hc * HS + ls, a.g.half - 1);
       const Site s = site_of(cb, a.out_par, a.g);
-      Cx<float> t[2][CIN][3];
+      if (d == 0) {
+        load_channels<CIN, CIN>(a.in_same, a.g.half, cb, 0, v);
+      } else if (d < 9) {
+        const int n0 = d0 == 0 ? 0 : neighbour(s, a.g, mu0, a.g.h1[mu0], d0 <= 4);
+        const int n1 = d0 == 8 ? 0 : neighbour(s, a.g, mu1, a.g.h1[mu1], d0 + 1 <= 4);
+        if (a.g.long12)
+          load_link<P32, true>(a.links, cb >> 6, k, cb & 63, 1.f, u);
+        else
+          load_link<P32, false>(a.links, cb >> 6, k, cb & 63, 1.f, u);
+        load_channels<CIN, CIN>(a.in_other, a.g.half, q ? n1 : n0, 0, v);
+      }
+      load_channels<COUT, GC>(gy, a.g.half, cb, gc0, gvs);
+    };
+    const int wv = b * NW + wave, step = 2 * nblk * NW;
+    int hc = 2 * wv;
+    if (hc < nhalf) load_half(hc);
+    while (hc < nhalf) {  // uniform per wave
+      Cx<float> t[CIN][3];
+      const bool live = hc * HS + ls < a.g.half;
+      const float sg = d > 4 ? -1.f : 1.f;
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const int d = d0 + q;
-        const bool have = q == 0 ? have0 : have1;
-        if (!have || !live) {
+      for (int e = 0; e < 9; ++e) u[e] = Cx<float>{sg * u[e].re, sg * u[e].im};
 #pragma unroll
-          for (int ci = 0; ci < CIN; ++ci)
+      for (int ci = 0; ci < CIN; ++ci) {
 #pragma unroll
-            for (int i = 0; i < 3; ++i) t[q][ci][i] = Cx<float>{0.f, 0.f};
-        } else if (d == 0) {
-          load_channels<CIN, CIN>(a.in_same, a.g.half, cb, 0, t[q]);
-        } else {
-          transported<CIN>(a, s, cb >> 6, cb & 63, d, t[q]);
+        for (int i = 0; i < 3; ++i) t[ci][i] = Cx<float>{0.f, 0.f};
+        matvec_acc(u, v[ci], t[ci]);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          if (d == 0) t[ci][i] = v[ci][i];
+          if (!live || d > 8) t[ci][i] = Cx<float>{0.f, 0.f};
         }
       }
-      Cx<float> gvs[COUT][3];
-      load_channels<COUT, COUT>(gy, a.g.half, cb, 0, gvs);
-      const int ls = lane & (HS - 1);
+      // entry n = 3 ls + i: step n / 2, k = 2 (n & 1) + part
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if ((lane >> 5) == h) {
+      for (int i = 0; i < 3; ++i) {
+        const int n = 3 * ls + i, at = 2 * (n & 1) * NS + (n >> 1);
 #pragma unroll
-          for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int ci = 0; ci < CIN; ++ci)
-#pragma unroll
-              for (int i = 0; i < 3; ++i) xs[wave][q][ci][3 * ls + i] = make_float2(t[q][ci][i].re, t[q][ci][i].im);
-#pragma unroll
-          for (int co = 0; co < COUT; ++co)
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-              gs[wave][co][3 * ls + i] = live ? make_float2(gvs[co][i].re, gvs[co][i].im) : make_float2(0.f, 0.f);
+        for (int ci = 0; ci < CIN; ++ci) {
+          xs[wave][q][ci][at] = t[ci][i].re;
+          xs[wave][q][ci][at + NS] = t[ci][i].im;
         }
-        __builtin_amdgcn_wave_barrier();
-        // inner step ks covers n = 2 ks + (kq >> 1), part = kq & 1
-#pragma unroll 8
-        for (int ks = 0; ks < 3 * HS / 2; ++ks) {
-          const int n = 2 * ks + (kq >> 1);
-          const float av = gsign == 0.f ? 0.f : gsign * gl[2 * n];
-          const float bv = bcol ? xl[2 * n] : 0.f;
-          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc, 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < (COUT >= 4 ? GC : 1); ++j) {
+          const Cx<float> gv = COUT >= 4 ? gvs[j][i] : (q ? gvs[1][i] : gvs[0][i]);
+          float* o = &gs[wave][COUT >= 4 ? gc0 + j : q][at];
+          o[0] = live ? gv.re : 0.f;
+          o[NS] = live ? gv.im : 0.f;
         }
-        __builtin_amdgcn_wave_barrier();
       }
+      __builtin_amdgcn_wave_barrier();
+      hc = hc & 1 ? hc - 1 + step : hc + 1;
+      if (hc < nhalf) load_half(hc);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < NS / 4; ++j) {
+        const f4v av = reinterpret_cast<const f4v*>(gl)[j], bv = reinterpret_cast<const f4v*>(xl)[j];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(gsign == 0.f ? 0.f : gsign * av[e], bcol ? bv[e] : 0.f, acc, 0, 0,
+                                                     0);
+      }
+      __builtin_amdgcn_wave_barrier();
     }
   }
   __syncthreads();
@@ -430,7 +510,7 @@ __global__ __launch_bounds__(kWgradMfmaWG, 2) void k_net_wgrad_mfma(NetLaunch l,
   for (int h = 0; h < 2; ++h) {
     const int co = 2 * kq + h;
     if (co >= COUT) continue;
-    const long idx = ((((long)a.out_par * 9 + d) * COUT + co) * CIN + cp) * gridDim.x + b;
+    const long idx = ((((long)a.out_par * 9 + d) * COUT + co) * CIN + cp) * nblk + b;
     partial[2 * idx] = v[2 * h];
     partial[2 * idx + 1] = v[2 * h + 1];
   }
@@ -458,19 +538,22 @@ __global__ __launch_bounds__(64) void k_net_wgrad_reduce(const double* partial, 
   out[2 * j + threadIdx.x] += sum;
 }
 
+// Place in a single-channel activation [3][V/2] of entry i of an even-site vector [V/2][3], n = 3 V/2.
+__device__ __forceinline__ long plane_of(long i, long n) { return (i % 3) * (n / 3) + i / 3; }
+
 // even-site complex128 vector -> channel 0 of a complex64 activation (parity 0)
 __global__ __launch_bounds__(256) void k_net_embed(const double2* in, float2* out, long n) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double2 v = in[i];
-  out[i] = make_float2((float)v.x, (float)v.y);
+  out[plane_of(i, n)] = make_float2((float)v.x, (float)v.y);
 }
 
 // channel 0 of a complex64 activation (parity 0) -> even-site complex128 vector
 __global__ __launch_bounds__(256) void k_net_extract(const float2* in, double2* out, long n) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const float2 v = in[i];
+  const float2 v = in[plane_of(i, n)];
   out[i] = make_double2((double)v.x, (double)v.y);
 }
 
@@ -481,11 +564,12 @@ __global__ __launch_bounds__(256) void k_net_loss(const float2* out, const doubl
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   double s[1] = {0.0};
   if (i < n) {
-    const float2 o = out[i];
+    const long j = plane_of(i, n);
+    const float2 o = out[j];
     const double2 xv = x[i];
     const double dr = (double)o.x - xv.x, di = (double)o.y - xv.y;
     s[0] = dr * dr + di * di;
-    g[i] = make_float2((float)(scale * dr), (float)(scale * di));
+    g[j] = make_float2((float)(scale * dr), (float)(scale * di));
   }
   block_sum<1>(s, lds);
   if (threadIdx.x == 0) partial[blockIdx.x] = s[0];
@@ -502,13 +586,17 @@ __global__ __launch_bounds__(256) void k_sum_partials(const double* partial, int
 // ---- launchers ---------------------------------------------------------------------
 hipError_t launch_net_layer(const NetLaunch& l, int cin, int cout, hipStream_t st) {
   if (l.n == 0) return hipSuccess;
-  const int nb = ceil_div(l.a[0].g.half, 256) * l.n;
+  const Geo& g = l.a[0].g;
+  const int nb = 8 * l.n * (int)((xcd_sweep_len(g.stride[3], g.L[3]) + 255) / 256);
   // layers with at least two channels on both sides mix on the matrix cores; 1 -> C and C -> 1
   // would fill at most a quarter of an MFMA tile and stay on the vector units
 #define STAG_NET_LAYER(I, O) \
   if (cin == I && cout == O) { k_net_layer<I, O><<<nb, 256, 0, st>>>(l); return hipGetLastError(); }
 #define STAG_NET_LAYER_MFMA(I, O) \
-  if (cin == I && cout == O) { k_net_layer_mfma<I, O><<<nb, 256, 0, st>>>(l); return hipGetLastError(); }
+  if (cin == I && cout == O) { \
+    for (int i = 0; i < l.n; ++i) \
+      if (!l.a[i].in_same || !l.a[i].in_other) return hipErrorInvalidValue;  /* inner layers: both parities set */ \
+    k_net_layer_mfma<I, O><<<nb, 256, 0, st>>>(l); return hipGetLastError(); }
   STAG_NET_LAYER(1, 1) STAG_NET_LAYER(1, 2) STAG_NET_LAYER(2, 1) STAG_NET_LAYER_MFMA(2, 2)
   STAG_NET_LAYER(1, 4) STAG_NET_LAYER(4, 1) STAG_NET_LAYER_MFMA(4, 4)
   STAG_NET_LAYER(1, 8) STAG_NET_LAYER(8, 1) STAG_NET_LAYER_MFMA(8, 8)
@@ -518,14 +606,17 @@ hipError_t launch_net_layer(const NetLaunch& l, int cin, int cout, hipStream_t s
 }
 
 hipError_t launch_net_wgrad(const NetLaunch& l, double* partial, int cin, int cout, int nblk, hipStream_t st) {
+  if (nblk % 8) return hipErrorInvalidValue;
 #define STAG_NET_WG(I, O)                                                          \
   if (cin == I && cout == O) {                                                     \
-    k_net_wgrad<I, O, O><<<dim3(nblk, 9, l.n), 256, 0, st>>>(l, partial);          \
+    k_net_wgrad<I, O, O><<<nblk * 9 * l.n, 256, 0, st>>>(l, partial, nblk);          \
     return hipGetLastError();                                                      \
   }
 #define STAG_NET_WG_MFMA(I, O)                                                     \
   if (cin == I && cout == O) {                                                     \
-    k_net_wgrad_mfma<I, O><<<dim3(nblk, 5, l.n), kWgradMfmaWG, 0, st>>>(l, partial); \
+    for (int i = 0; i < l.n; ++i) /* inner layers: both parities set */            \
+      if (!l.a[i].in_same || !l.a[i].in_other) return hipErrorInvalidValue;        \
+    k_net_wgrad_mfma<I, O><<<nblk * 5 * l.n, kWgradMfmaWG, 0, st>>>(l, partial, nblk); \
     return hipGetLastError();                                                      \
   }
   STAG_NET_WG(1, 1) STAG_NET_WG(1, 2) STAG_NET_WG(2, 1) STAG_NET_WG_MFMA(2, 2)
@@ -615,12 +706,12 @@ __global__ __launch_bounds__(256) void k_sub_norm(const double2* a, const double
   if (threadIdx.x == 0) partial[blockIdx.x] = s[0];
 }
 
-// complex128 -> complex64 times a real scale
+// even-site complex128 vector times a real scale -> single-channel complex64 activation
 __global__ __launch_bounds__(256) void k_scale_to_f32(const double2* in, double scale, float2* out, long n) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const double2 v = in[i];
-  out[i] = make_float2((float)(scale * v.x), (float)(scale * v.y));
+  out[plane_of(i, n)] = make_float2((float)(scale * v.x), (float)(scale * v.y));
 }
 
 hipError_t launch_sub_norm(const void* a, const void* b, void* out, double* partial, double* sum, long nsites,

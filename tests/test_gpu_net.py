@@ -95,6 +95,31 @@ def test_net_loss_and_gradients_match_oracle(gpu_lib, dims, width):
         assert rel(g, gr) <= 1e-4
 
 
+@pytest.mark.parametrize("dims,width", [((2, 6, 6, 4), 8), ((6, 2, 2, 10), 2), ((10, 14, 18, 26), 4)])
+def test_net_uneven_ranges_match_oracle(gpu_lib, dims, width):
+    """Time slices that the eight XCD ranges divide unevenly (36, 12 and 1260 sites per parity), a ragged last
+    wave, and (10x14x18x26, 512 chunks of 64 sites) gradient waves with a second chunk: forward within
+    fp32_bound, loss and gradients to the bounds of the test above."""
+    from paper_1010_4782_amd.stagcg import Net
+
+    print(f"net uneven ranges {dims} width {width}", flush=True)
+    lat, fat, _ = setup(dims, 27)
+    channels = [1, width, width, 1]
+    net = Net(lat, layers=3, channels=width)
+    W32 = [quant.to_f32(w) for w in init_weights(channels, 28, scale=1.0)]
+    net.set_weights(W32)
+    b, x = gaussian_source(dims, 29, 1), gaussian_source(dims, 30, 1)
+    Ft = quant.to_f32(folded_fat(fat, dims))
+    b32 = quant.to_f32(b[0])
+    out = net.apply(torch.from_numpy(b).cuda()).cpu().numpy()
+    assert_within(out[0], net_forward(Ft, W32, b32, dims), fp32_bound(Ft, W32, b32, dims))
+    loss, grads = net.loss_grad(torch.from_numpy(b).cuda(), torch.from_numpy(x).cuda())
+    L, G = loss_and_grads(Ft, W32, [(b32, x[0])], dims)
+    assert abs(loss - L) <= 1e-5 * abs(L)
+    for g, gr in zip(grads, G):
+        assert rel(g, gr) <= 1e-4
+
+
 def test_net_residual_loss_matches_oracle(gpu_lib):
     from paper_1010_4782_amd.stagcg import Net
 
