@@ -1,0 +1,235 @@
+// CG iterations of small problems with the scalar steps inside the vector kernels.
+//
+// On a small lattice an iteration of the general path (Dslash, Dslash + <d, Ad>, finalize, r update,
+// finalize, x and d update) is six launches of 3.3-6 us that each wait on a chain of memory round trips; the
+// two finalize launches, one workgroup each, take 5.7 us of it apiece.  With at most kFusedTiles partial sums
+// per right-hand side, every workgroup that needs alpha or beta adds the partials itself, in k_finalize's
+// order, and one of them writes the slot's scalars:
+//   k_resid  alpha from the <d, Ad> partials; r -= alpha Ad; |r|^2 partials
+//   k_xd     beta from the |r|^2 partials and the stopping test; x += alpha d; d = r + beta d
+// Every sum and product is taken in the order and precision of the general kernels: the same bits.  An FP64
+// iteration at 8^4 takes 24.4 us instead of 32.9, an FP16 one at 16^3x32 46.0 instead of 52.8.  Forming
+// r + beta d inside the first operator launch too (three launches) was slower from 12^4 on: 33.8 us against
+// 29.4, the reads of two vectors at 16 neighbours cost more than a launch.
+//
+// The scalars are double-buffered: k_xd reads one bank and its writer fills the other, so no workgroup can see
+// another's update of what it is still reading.  k_resid writes alpha, <d, Ad> and a state that only ever
+// leaves 0 or 1 for 2, none of which its other workgroups act on differently: a state of 1 or 2 stops them
+// either way, and a breakdown is in the sum they all form.
+#include "device.h"
+#include "launch.h"
+
+namespace stag {
+
+namespace {
+
+// The sum of src[0..n), n <= kFusedTiles, as k_finalize forms it: 1024 lanes with one partial each, a butterfly
+// per wave of 64, the waves in order.  Valid in every thread; blockDim.x is a multiple of 64.
+__device__ __forceinline__ double sum_partials(const double* src, int n, double* lds /* >= 16 */) {
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave, nw = blockDim.x / kWave;
+  const int nv = ceil_div(n, kWave);
+  for (int w = wave; w < nv; w += nw) {
+    double v[1] = {w * kWave + lane < n ? src[w * kWave + lane] : 0.0};
+    wave_sum<1>(v);
+    if (lane == 0) lds[w] = v[0];
+  }
+  __syncthreads();
+  double s = lds[0];
+  for (int w = 1; w < nv; ++w) s += lds[w];
+  return s;
+}
+
+struct Slot {
+  const ProbDev* pd;
+  int tile, r, slot;
+};
+__device__ __forceinline__ Slot slot_of_block(const Batch& B, int bid) {
+  Slot m;
+  const int p = find_problem(B, bid);
+  m.pd = B.probs + p;
+  const int local = bid - B.block_start[p], groups = B.groups[p];
+  m.tile = local / groups;
+  m.r = local - m.tile * groups;
+  m.slot = m.pd->slot0 + m.r;
+  return m;
+}
+__device__ __forceinline__ const double* partials(const Batch& B, int slot, int kind) {
+  return B.partial + ((long)slot * kPartialSlots + kind) * B.pstride;
+}
+
+// Beta and the stopping test of a slot (k_finalize's FIN_BETA).  Returns the state after it (2 if the slot was
+// not running) and beta; the workgroup of tile 0 writes the slot's scalars to the other bank.
+__device__ __forceinline__ int beta_step(const Batch& B, const Slot& m, Scal* next, double* hist, int hist_stride,
+                                         double* lds, double& beta) {
+  const Scal& pre = B.scal[m.slot];
+  const int st = pre.state;
+  const double delta0 = pre.delta, thr0 = pre.thr, rel0 = pre.rel_thr;
+  const int iter0 = pre.iter, max0 = pre.max_iter;
+  double sum = 0.0;
+  int now = st, flags = pre.flags;
+  beta = 0.0;
+  if (st == 0) {  // uniform
+    sum = sum_partials(partials(B, m.slot, 1), ceil_div(m.pd->g.half, kMaxWG), lds);
+    if (!isfinite(sum)) {
+      now = 2;
+      flags |= kFlagNaN;
+    } else {
+      beta = sum / delta0;
+      if (sum <= thr0) now = 1;
+      if (sum <= rel0) {
+        now = 1;
+        flags |= kFlagRelDue;
+      }
+      if (iter0 + 1 >= max0) {
+        now = 1;
+        flags |= kFlagMaxIter;
+      }
+    }
+  }
+  if (m.tile == 0 && threadIdx.x == 0) {
+    // every word of the slot, then the ones that changed
+    constexpr int kWords = sizeof(Scal) / 8;
+    const double* from = reinterpret_cast<const double*>(&pre);
+    double* to = reinterpret_cast<double*>(next + m.slot);
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) to[i] = from[i];
+    if (st == 0) {
+      Scal& sc = next[m.slot];
+      sc.state = now;
+      sc.flags = flags;
+      if (now != 2) {
+        sc.delta_old = delta0;
+        sc.delta = sum;
+        sc.beta = beta;
+        sc.iter = iter0 + 1;
+        if (hist && iter0 < pre.hist_len) hist[((long)m.slot * hist_stride + iter0) * 2 + 1] = beta;
+      }
+    }
+  }
+  return st == 0 ? now : 2;
+}
+
+// alpha (or, for a slot the stopping test ended, state 1 -> 2), r -= alpha Ad, partial |r|^2.  dot_wg: sites
+// per <d, Ad> partial.
+template <int P>
+__global__ __launch_bounds__(kMaxWG) void k_resid(Batch B, int r_id, int dot_wg, double* hist, int hist_stride) {
+  using T = typename RealOf<P>::T;
+  constexpr bool kNT = P != P64;  // as in k_update_r
+  __shared__ double lds[kFusedTiles / kWave];
+  const Slot m = slot_of_block(B, blockIdx.x);
+  Scal& sc = B.scal[m.slot];
+  const int st = sc.state;
+  const double delta = sc.delta;
+  const bool writer = m.tile == 0 && threadIdx.x == 0;
+  if (st != 0) {  // uniform
+    if (st == 1 && writer) sc.state = 2;
+    return;
+  }
+  const int half = m.pd->g.half;
+  const long off = (long)m.r * half * spinor_bytes(P);
+  const int cb_raw = m.tile * kMaxWG + threadIdx.x;
+  const bool live = cb_raw < half;
+  char* rp = reinterpret_cast<char*>(m.pd->vec[r_id]) + off;
+  Cx<T> r[3], ad[3];
+  if (live) {
+    load_spinor<P, kNT>(rp, cb_raw, r);
+    load_spinor<P, kNT>(reinterpret_cast<const char*>(m.pd->vec[V_AD]) + off, cb_raw, ad);
+  }
+  const double dAd = sum_partials(partials(B, m.slot, 0), ceil_div(half, dot_wg), lds);
+  const bool ok = dAd > 0.0 && isfinite(dAd);
+  const double alpha = delta / dAd;
+  if (writer) {
+    sc.dAd = dAd;
+    if (ok) {
+      sc.alpha = alpha;
+      if (hist && sc.iter < sc.hist_len) hist[((long)m.slot * hist_stride + sc.iter) * 2] = alpha;
+    } else {
+      sc.flags |= kFlagNaN;
+      sc.state = 2;
+    }
+  }
+  if (!ok) return;  // uniform
+  const T al = (T)alpha;
+  double s[1] = {0.0};
+  if (live) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      r[c].re = fma(-al, ad[c].re, r[c].re);
+      r[c].im = fma(-al, ad[c].im, r[c].im);
+    }
+    store_spinor<P, kNT>(rp, cb_raw, r);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) s[0] += (double)r[c].re * r[c].re + (double)r[c].im * r[c].im;
+  }
+  __syncthreads();  // lds is read above
+  block_sum<1>(s, lds);
+  if (threadIdx.x == 0) B.partial[((long)m.slot * kPartialSlots + 1) * B.pstride + m.tile] = s[0];
+}
+
+// beta and the stopping test, x += alpha d, d = r + beta d.
+template <int P, int PX>
+__global__ __launch_bounds__(kMaxWG) void k_xd(Batch B, Scal* next, int x_id, int r_id, double* hist,
+                                               int hist_stride) {
+  using T = typename RealOf<P>::T;
+  using TX = typename RealOf<PX>::T;
+  constexpr bool kNT = P != P64;  // as in k_update_xd
+  __shared__ double lds[kFusedTiles / kWave];
+  const Slot m = slot_of_block(B, blockIdx.x);
+  const int half = m.pd->g.half;
+  const int cb = m.tile * kMaxWG + threadIdx.x;
+  const TX alpha = (TX)B.scal[m.slot].alpha;
+  double b64;
+  const int now = beta_step(B, m, next, hist, hist_stride, lds, b64);
+  if (now > 1 || cb >= half) return;
+  const T beta = (T)b64;
+  char* dp = reinterpret_cast<char*>(m.pd->vec[V_D]) + (long)m.r * half * spinor_bytes(P);
+  char* xp = reinterpret_cast<char*>(m.pd->vec[x_id]) + (long)m.r * half * spinor_bytes(PX);
+  Cx<T> d[3], r[3];
+  Cx<TX> x[3];
+  load_spinor<P, kNT>(dp, cb, d);
+  load_spinor<P, kNT>(reinterpret_cast<const char*>(m.pd->vec[r_id]) + (long)m.r * half * spinor_bytes(P), cb, r);
+  load_spinor<PX, kNT>(xp, cb, x);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    x[c].re = fma(alpha, (TX)d[c].re, x[c].re);
+    x[c].im = fma(alpha, (TX)d[c].im, x[c].im);
+    d[c].re = fma(beta, d[c].re, r[c].re);
+    d[c].im = fma(beta, d[c].im, r[c].im);
+  }
+  store_spinor<PX, kNT>(xp, cb, x);
+  store_spinor<P, kNT>(dp, cb, d);
+}
+
+int blocks_of(const Batch& B) { return B.block_start[B.nprob]; }
+
+}  // namespace
+
+hipError_t launch_fused_resid(const BatchHost& bh, int prec, int dot_wg, double* hist, int hist_stride,
+                              hipStream_t st) {
+  const Batch B = make_batch(bh, kMaxWG, 1);
+  const int nb = blocks_of(B);
+  if (nb == 0) return hipSuccess;
+  switch (prec) {
+    case P64: k_resid<P64><<<nb, kMaxWG, 0, st>>>(B, V_R, dot_wg, hist, hist_stride); break;
+    case P32: k_resid<P32><<<nb, kMaxWG, 0, st>>>(B, V_RL, dot_wg, hist, hist_stride); break;
+    case P16: k_resid<P16><<<nb, kMaxWG, 0, st>>>(B, V_RL, dot_wg, hist, hist_stride); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_fused_xd(const BatchHost& bh, Scal* next, int prec, int x_id, double* hist, int hist_stride,
+                           hipStream_t st) {
+  const Batch B = make_batch(bh, kMaxWG, 1);
+  const int nb = blocks_of(B);
+  if (nb == 0) return hipSuccess;
+  switch (prec) {
+    case P64: k_xd<P64, P64><<<nb, kMaxWG, 0, st>>>(B, next, x_id, V_R, hist, hist_stride); break;
+    case P32: k_xd<P32, P32><<<nb, kMaxWG, 0, st>>>(B, next, x_id, V_RL, hist, hist_stride); break;
+    case P16: k_xd<P16, P32><<<nb, kMaxWG, 0, st>>>(B, next, x_id, V_RL, hist, hist_stride); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace stag

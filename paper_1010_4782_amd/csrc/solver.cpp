@@ -33,6 +33,8 @@ struct Run {
   std::vector<hipEvent_t>* events = nullptr;
   size_t ev_used = 0;
   Scal* h_scal = nullptr;
+  Scal* scal_bank[2] = {};  // the two banks of device scalars; bh.d_scal is the current one
+  bool fused = false;       // iterations run on the fused kernels (cg_fused.hip)
 };
 
 stag_status fail_arg(const std::string& m) {
@@ -104,6 +106,36 @@ hipError_t iteration(Run& R, int x_prec, int x_id, double* d_hist) {
   if (e == hipSuccess) e = launch_update_r(R.bh, P, kVecWG, R.st);
   if (e == hipSuccess) e = launch_finalize(R.bh, FIN_BETA, 1, 1, kVecWG, d_hist, R.hist_len, R.st);
   if (e == hipSuccess) e = launch_update_xd(R.bh, P, x_prec, x_id, kVecWG, R.st);
+  return e;
+}
+
+// Whether a batch's iterations run on the fused kernels (cg_fused.hip), which add the partials of a reduction
+// in every workgroup: up to kFusedTiles <d, Ad> partials per right-hand side (65536 sites of one parity in
+// 64-site workgroups), where the sums still cost less than the two launches they save (16^3x32: 46.0 us an
+// FP16 iteration against 52.8).  Sampled profiles keep the general path.
+bool fused_ok(const Run& R) {
+  if (R.profile_every > 0) return false;
+  for (const HostProb& p : R.bh.probs)
+    if (ceil_div(p.half, std::min(partial_wg(R.shape), kVecWG)) > kFusedTiles) return false;
+  return true;
+}
+
+// n CG iterations (x accumulated in precision x_prec at x_id), from and to the state between iterations.
+hipError_t iterations(Run& R, int n, int x_prec, int x_id, double* d_hist) {
+  hipError_t e = hipSuccess;
+  for (int i = 0; i < n && e == hipSuccess; ++i) {
+    if (!R.fused) {
+      e = iteration(R, x_prec, x_id, d_hist);
+      continue;
+    }
+    const int P = R.prec;
+    e = launch_dslash(R.bh, P, EPI_PLAIN, 1, V_D, V_T, 0, 0, 1, R.shape, R.st);
+    if (e == hipSuccess) e = launch_dslash(R.bh, P, EPI_XPAY_DOT, 0, V_T, V_AD, V_D, 0, 1, R.shape, R.st);
+    if (e == hipSuccess) e = launch_fused_resid(R.bh, P, partial_wg(R.shape), d_hist, R.hist_len, R.st);
+    Scal* next = R.bh.d_scal == R.scal_bank[0] ? R.scal_bank[1] : R.scal_bank[0];
+    if (e == hipSuccess) e = launch_fused_xd(R.bh, next, P, x_id, d_hist, R.hist_len, R.st);
+    R.bh.d_scal = next;
+  }
   return e;
 }
 
@@ -400,7 +432,7 @@ stag_status solve_batch(int nprob, const stag_problem* probs, const stag_cg_para
   R.bh.long12 = probs[0].lat->g.long12 != 0;
   R.bh.pstride = ceil_div(max_half, kWave / 2);  // 32-site partials of the time-streaming kernel
   STAG_HIP_TRY(ctl.probs.ensure(sizeof(ProbDev) * kMaxProb));
-  STAG_HIP_TRY(ctl.scal.ensure(sizeof(Scal) * nslots));
+  STAG_HIP_TRY(ctl.scal.ensure(sizeof(Scal) * 2 * nslots));
   STAG_HIP_TRY(ctl.partial.ensure(sizeof(double) * (size_t)nslots * kPartialSlots * R.bh.pstride));
   STAG_HIP_TRY(ctl.h_scal.ensure(sizeof(Scal) * nslots));
   STAG_HIP_TRY(ctl.h_probs.ensure(sizeof(ProbDev) * kMaxProb));
@@ -412,6 +444,8 @@ stag_status solve_batch(int nprob, const stag_problem* probs, const stag_cg_para
   }
   R.bh.d_probs = reinterpret_cast<const ProbDev*>(ctl.probs.ptr);
   R.bh.d_scal = reinterpret_cast<Scal*>(ctl.scal.ptr);
+  R.scal_bank[0] = R.bh.d_scal;
+  R.scal_bank[1] = R.bh.d_scal + nslots;
   R.bh.d_partial = reinterpret_cast<double*>(ctl.partial.ptr);
   R.h_scal = reinterpret_cast<Scal*>(ctl.h_scal.ptr);
   R.events = &probs[0].lat->prof_events;
@@ -428,6 +462,7 @@ stag_status solve_batch(int nprob, const stag_problem* probs, const stag_cg_para
     if (prm.autotune && mixed && !has_shape(key64))
       STAG_HIP_TRY(tune_batch(R.bh, key64, P64, st, nullptr, nullptr, V_X, V_TMPO));
     R.shape64 = lookup_shape(R.bh, key64, P64);
+    R.fused = fused_ok(R);
   }
 
   // ---- scalars ----
@@ -505,7 +540,7 @@ stag_status solve_batch(int nprob, const stag_problem* probs, const stag_cg_para
     if (!mixed) {
       STAG_HIP_TRY(launch_copy_vec(R.bh, P64, V_R, P64, V_D, 1, kVecWG, st));
       for (;;) {
-        for (int i = 0; i < prm.check_interval; ++i) STAG_HIP_TRY(iteration(R, x_prec, x_id, d_hist));
+        STAG_HIP_TRY(iterations(R, prm.check_interval, x_prec, x_id, d_hist));
         STAG_HIP_TRY(pull_scal(R));
         bool running = false;
         for (int s = 0; s < nslots; ++s) running |= R.h_scal[s].state == 0;
@@ -523,7 +558,7 @@ stag_status solve_batch(int nprob, const stag_problem* probs, const stag_cg_para
         // a batch ends where the next interval-driven reliable update is due, so that it comes after
         // exactly reliable_interval iterations, not at the next multiple of check_interval
         const int batch = std::min(prm.check_interval, std::max(1, prm.reliable_interval - since));
-        for (int i = 0; i < batch; ++i) STAG_HIP_TRY(iteration(R, x_prec, x_id, d_hist));
+        STAG_HIP_TRY(iterations(R, batch, x_prec, x_id, d_hist));
         since += batch;
         STAG_HIP_TRY(pull_scal(R, "poll-mp"));
         // Slots that stopped (apparent convergence, residual drop, iteration cap) wait for a
