@@ -9,6 +9,8 @@
 // with s(m,k) = (-1)^floor((m_t + k)/L_t) for the time direction when it is
 // antiperiodic and 1 otherwise.  Back links are duplicated per output parity so
 // the Dslash streams exactly 16 matrices per site, coalesced (Sec. 3.1).
+#include <type_traits>
+
 #include "device.h"
 #include "launch.h"
 
@@ -35,161 +37,208 @@ Geo make_geo(const int dims[4]) {
   return g;
 }
 
-// Folded matrix k at output site s (FP64).
-__device__ void folded_link(const double2* fat, const double2* lng, double naik, const Geo& g, int antiper,
-                            const Site& s, int k, double2 u[9]) {
-  const int mu = k >> 2, j = k & 3;
-  const bool is_long = j >= 2, bwd = (j & 1) != 0;
-  const int hop = is_long ? 3 : 1;
-  const double2* src = is_long ? lng : fat;
-  if (src == nullptr) {
-#pragma unroll
-    for (int e = 0; e < 9; ++e) u[e] = make_double2(0.0, 0.0);
-    return;
-  }
-  int c[4] = {s.x, s.y, s.z, s.t};
-  const int eta_sum = (mu > 0 ? c[0] : 0) + (mu > 1 ? c[1] : 0) + (mu > 2 ? c[2] : 0);
-  double coef = (eta_sum & 1) ? -1.0 : 1.0;
-  if (is_long) coef *= naik;
-  if (bwd) {
-    c[mu] = ((c[mu] - hop) % g.L[mu] + g.L[mu]) % g.L[mu];  // start site m = n - hop mu
-    coef = -coef;
-  }
-  if (mu == 3 && antiper && (((c[3] + hop) / g.L[3]) & 1)) coef = -coef;
-  const long site = (((long)c[3] * g.L[2] + c[2]) * g.L[1] + c[1]) * g.L[0] + c[0];
-  const long vol = (long)g.half * 2;
-  const double2* U = src + ((long)mu * vol + site) * 9;
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      // forward: U[a][b]; backward: (U^dag)[a][b] = conj(U[b][a])
-      const double2 w = bwd ? U[3 * b + a] : U[3 * a + b];
-      u[3 * a + b] = make_double2(coef * w.x, bwd ? -coef * w.y : coef * w.y);
-    }
-}
-
-// binary16 code of v / s with the quotient rounded first to binary32 (both round-to-nearest-even).
+// binary16 code of v / s, the quotient in binary64 (the compiler contracts the two conversions into one
+// rounding, to nearest even).
 __device__ __forceinline__ _Float16 f16_code(double v, float s) {
   return s > 0.f ? (_Float16)(float)(v / (double)s) : (_Float16)0.f;
 }
 
-template <int P>
-__global__ __launch_bounds__(256) void k_pack_links(const double2* fat, const double2* lng, double naik, Geo g,
-                                                    int antiper, int par, char* out, float* lscale) {
-  const int cb_raw = blockIdx.x * blockDim.x + threadIdx.x;
-  const int padded = ceil_div(g.half, kWave) * kWave;
-  if (cb_raw >= padded) return;
-  const bool live = cb_raw < g.half;
-  const Site s = site_of(live ? cb_raw : 0, par, g);
-  const long blk = cb_raw >> 6;
-  const int lane = cb_raw & 63;
-  float scale[2] = {0.f, 0.f};
+// The same code from y = RN(1 / s), s finite and positive, without a division and with the conversion
+// instructions instead of the dozens of integer ones that a binary64 -> binary16 rounding expands to.
+//  * q = RN(v y) is within two units of v / s in the last place, one step q + RN(v - q s) y brings it within
+//    one, and the second then gives RN(v / s) itself (Markstein 1990: the remainder of a faithful quotient is
+//    exact, and the corrected quotient correctly rounded when y is).
+//  * q goes to binary32 rounded to odd (an inexact result takes the neighbour whose last bit is set), which
+//    keeps enough of q for the rounding to binary16 to be the direct one (two more bits than the result
+//    suffice, Boldo and Melquiond 2008).
+__device__ __forceinline__ unsigned short f16_code_y(double v, double s, double y) {
+  double q = v * y;
+  q = fma(fma(-q, s, v), y, q);
+  q = fma(fma(-q, s, v), y, q);
+  const float f = (float)q;
+  const double d = fabs((double)f), a = fabs(q);
+  unsigned w = __float_as_uint(f);
+  const unsigned moved = d < a ? w + 1u : (d > a ? w - 1u : w);
+  w = (w & 1u) ? w : moved;
+  return __builtin_bit_cast(unsigned short, (_Float16)__uint_as_float(w));
+}
+
+// Packs the links of one block of 64 output sites and both parities in every requested precision (FP64 always).
+// A wave takes 32 sites of one parity with two lanes per site: lane half h loads, folds and stores the four
+// matrices of directions 2h and 2h + 1 of a group (one-hop, then three-hop).  The four waves of a block read
+// the same cache lines: the sites of the other parity lie in between.  A wave's 64 source matrices (144 B each,
+// at sites that are neighbours but for lattice edges) are loaded as 9 x 1 KiB with consecutive lanes on
+// consecutive 16-byte words, the next matrix already in flight, and handed to their lanes through LDS; one
+// lane per matrix would touch 64 cache lines per load.
+// The FP16 scales need all eight matrices of a group (largest |re|, |im| over the stored entries of an output
+// site's one-hop and, separately, three-hop matrices, rounded to binary32), so with FP16 a lane's four stay in
+// registers (144 VGPRs) instead of being read back from the FP64 blocks.
+// Lanes past the lattice pack site 0 into the padding, which nothing reads.
+// Bound by its traffic: 8.2 GB beyond L2 at 28^3x96 (FP64 + FP16, two-row long links: 5 GB of it the packed
+// links) in 1.63 ms, 5 TB/s.  One pass per parity and precision, a lane per output site gathering 144-byte
+// matrices and the FP16 pass reading the FP64 blocks back, took 3.02 ms.
+template <bool W32, bool W16>
+__global__ __launch_bounds__(4 * kWave, 2) void k_pack_links(const double2* fat, const double2* lng, double naik,
+                                                             Geo g, PackOut out) {
+  __shared__ d2v lds[4][9 * kWave];
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int par = wave & 1, h = lane >> 5;
+  const long blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int bl = 32 * (wave >> 1) + (lane & 31);  // this lane's site within the block
+  const int cb_raw = (int)blk * kWave + bl;
+  const Site s = site_of(cb_raw < g.half ? cb_raw : 0, par, g);
+  const long vol9 = (long)g.half * 18;
+  const long lex = (((long)s.t * g.L[2] + s.z) * g.L[1] + s.y) * g.L[0] + s.x;
   const bool c12 = g.long12 != 0;
-  // FP64 with lscale: also compute the FP16 scales of the same matrices for k_pack_f16_from_f64, per
-  // output site the largest |re|, |im| over the stored entries of its eight one-hop and, separately, its
-  // eight three-hop matrices (rounded to binary32: the rounding of a max is the max of the roundings)
-  const bool scales64 = P == P64 && lscale != nullptr;
-  for (int k = 0; k < kLinks; ++k) {
-    double2 u[9];
-    if (live) {
-      folded_link(fat, lng, naik, g, antiper, s, k, u);
-    } else {
+  d2v* stage = lds[wave];
+  // this lane's two directions, q = 0, 1: mu = 2 h + q
+  int c[2], L[2], stride[2], eta[2];
+  c[0] = h ? s.z : s.x;
+  c[1] = h ? s.t : s.y;
+  L[0] = h ? g.L[2] : g.L[0];
+  L[1] = h ? g.L[3] : g.L[1];
+  stride[0] = h ? g.L[0] * g.L[1] : 1;
+  stride[1] = h ? g.L[0] * g.L[1] * g.L[2] : g.L[0];
+  eta[0] = h ? (s.x + s.y) & 1 : 0;
+  eta[1] = h ? (s.x + s.y + s.z) & 1 : s.x & 1;
+  // which lane's matrix, and which of its words, this lane loads in step i
+  int owner[9], word[9];
 #pragma unroll
-      for (int e = 0; e < 9; ++e) u[e] = make_double2(0.0, 0.0);
-    }
-    char* base = out + link_slot_offset(P, c12, blk, k);
-    const bool two_rows = c12 && ((k & 3) >= 2);
-    if (P == P64) {
-      double2* o = reinterpret_cast<double2*>(base) + lane;
+  for (int i = 0; i < 9; ++i) {
+    owner[i] = (i * kWave + lane) / 9;
+    word[i] = i * kWave + lane - 9 * owner[i];
+  }
+  // start coordinate of the lane's j-th matrix (direction q = j / 2, odd j backward: n - hop mu)
+  auto start = [&](int j, int hop) {
+    const int q = j >> 1;
+    return (j & 1) ? ((c[q] - hop) % L[q] + L[q]) % L[q] : c[q];
+  };
+  auto load = [&](const double2* field, int j, int hop, d2v (&w)[9]) {
+    const int q = j >> 1;
+    const long at = (2 * h + q) * vol9 + 9 * (lex + (long)(start(j, hop) - c[q]) * stride[q]);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) w[i] = as_global<d2v>(field)[__shfl(at, owner[i], kWave) + word[i]];
+  };
+  d2v next[9];
+  load(fat, 0, 1, next);
+  auto group = [&](auto which) {
+    constexpr int grp = decltype(which)::value;  // 0: one-hop, 1: three-hop matrices
+    constexpr int hop = grp ? 3 : 1;
+    const bool two_rows = c12 && grp == 1, have = grp == 0 || lng != nullptr;
+    d2v u[W16 ? 4 : 1][9];
+    float scale = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      d2v(&v)[9] = u[W16 ? j : 0];
+      const int k0 = 4 * (j >> 1) + (j & 1) + 2 * grp;  // matrix index of the lower half; the upper's is 8 more
+      if (have) {  // uniform
+#pragma unroll
+        for (int i = 0; i < 9; ++i) stage[i * kWave + lane] = next[i];
+        __builtin_amdgcn_wave_barrier();
+        if (j < 3)
+          load(grp ? lng : fat, j + 1, hop, next);
+        else if (grp == 0 && lng)
+          load(lng, 0, 3, next);
+        // folded matrix: eta, boundary sign, c_N; the backward one daggered and negated
+        double coef = eta[j >> 1] ? -1.0 : 1.0;
+        if (grp == 1) coef *= naik;
+        if (j & 1) coef = -coef;
+        if ((j >> 1) == 1 && h && g.antiper && (((start(j, hop) + hop) / L[1]) & 1)) coef = -coef;
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+          for (int b = 0; b < 3; ++b) {
+            // forward: U[a][b]; backward: (U^dag)[a][b] = conj(U[b][a])
+            const d2v w = stage[9 * lane + ((j & 1) ? 3 * b + a : 3 * a + b)];
+            v[3 * a + b] = d2v{coef * w.x, (j & 1) ? -coef * w.y : coef * w.y};
+          }
+        __builtin_amdgcn_wave_barrier();
+      } else {
+#pragma unroll
+        for (int e = 0; e < 9; ++e) v[e] = d2v{0.0, 0.0};
+      }
+      gptr_w<d2v> o = as_global_w<d2v>(out.f64[par] + link_slot_offset(P64, c12, blk, k0 + 8 * h)) + bl;
 #pragma unroll
       for (int e = 0; e < 9; ++e)
-        if (e < (two_rows ? 6 : 9)) o[e * kWave] = u[e];
-      if (scales64 && live) {
-        double m = 0.0;
+        if (!two_rows || e < 6) __builtin_nontemporal_store(v[e], o + e * kWave);
+      if constexpr (W32) {
+        char* base = out.f32[par] + link_slot_offset(P32, c12, blk, k0 + 8 * h);
+        gptr_w<f4v> q = as_global_w<f4v>(base) + bl;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (!two_rows || e < 3)
+            __builtin_nontemporal_store(f4v{(float)v[2 * e].x, (float)v[2 * e].y, (float)v[2 * e + 1].x, (float)v[2 * e + 1].y},
+                                        q + e * kWave);
+        if (!two_rows)
+          __builtin_nontemporal_store(f2v{(float)v[8].x, (float)v[8].y}, as_global_w<f2v>(base + 4 * kWave * 16) + bl);
+      }
+      if constexpr (W16) {
+        double mx = 0.0;
 #pragma unroll
         for (int e = 0; e < 9; ++e)
-          if (e < (two_rows ? 6 : 9)) m = fmax(m, fmax(fabs(u[e].x), fabs(u[e].y)));
-        scale[(k >> 1) & 1] = fmaxf(scale[(k >> 1) & 1], (float)m);
+          if (!two_rows || e < 6) mx = fmax(mx, fmax(fabs(v[e].x), fabs(v[e].y)));
+        scale = fmaxf(scale, (float)mx);
       }
-    } else {
-      static_assert(P == P64 || P == P32, "FP16 is packed from the FP64 matrices (k_pack_f16_from_f64)");
-      float4* o = reinterpret_cast<float4*>(base) + lane;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (j < (two_rows ? 3 : 4))
-          o[j * kWave] = make_float4((float)u[2 * j].x, (float)u[2 * j].y, (float)u[2 * j + 1].x, (float)u[2 * j + 1].y);
-      if (!two_rows) reinterpret_cast<float2*>(base + 4 * kWave * 16)[lane] = make_float2((float)u[8].x, (float)u[8].y);
     }
-  }
-  if (scales64) {
-    lscale[blk * 2 * kWave + lane] = scale[0];
-    lscale[blk * 2 * kWave + kWave + lane] = scale[1];
-  }
+    if constexpr (W16) {
+      scale = fmaxf(scale, __shfl_xor(scale, 32, kWave));
+      if (h == 0)
+        __builtin_nontemporal_store(scale, as_global_w<float>(out.scale[par]) + (blk * 2 + grp) * kWave + bl);
+      const bool fast = scale > 0.f && scale < __builtin_inff();
+      const double sd = (double)scale, y = 1.0 / sd;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        unsigned w[9];
+        if (fast) {
+#pragma unroll
+          for (int e = 0; e < 9; ++e)
+            w[e] = f16_code_y(u[j][e].x, sd, y) | (unsigned)f16_code_y(u[j][e].y, sd, y) << 16;
+        } else {  // a zero group, or one past binary32's range
+#pragma unroll 1
+          for (int e = 0; e < 9; ++e) {
+            h2v q;
+            q.x = f16_code(u[j][0].x, scale);
+            q.y = f16_code(u[j][0].y, scale);
+            const d2v first = u[j][0];  // rotate: the registers are indexed statically
+            const unsigned code = __builtin_bit_cast(unsigned, q);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) u[j][i] = u[j][i + 1];
+            u[j][8] = first;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) w[i] = w[i + 1];
+            w[8] = code;
+          }
+        }
+        char* base = out.f16[par] + link_slot_offset(P16, c12, blk, 4 * (j >> 1) + (j & 1) + 2 * grp + 8 * h);
+        gptr_w<u4v> q = as_global_w<u4v>(base) + bl;
+        __builtin_nontemporal_store(u4v{w[0], w[1], w[2], w[3]}, q);
+        if (two_rows) {
+          __builtin_nontemporal_store(u2v{w[4], w[5]}, as_global_w<u2v>(base + kWave * 16) + bl);
+        } else {
+          __builtin_nontemporal_store(u4v{w[4], w[5], w[6], w[7]}, q + kWave);
+          __builtin_nontemporal_store(w[8], as_global_w<unsigned>(base + 2 * kWave * 16) + bl);
+        }
+      }
+    }
+  };
+  group(std::integral_constant<int, 0>{});
+  group(std::integral_constant<int, 1>{});
 }
 
-// FP16 packing from the FP64 packed matrices and the scales the FP64 pack computed (when both are
-// requested): one coalesced pass over the packed FP64 blocks instead of folding every link again from
-// the input fields twice (once for the scales, once for the codes).  The codes are the same, since the
-// FP64 packed entries are the folded matrices themselves.
-__global__ __launch_bounds__(256) void k_pack_f16_from_f64(const char* packed64, const float* lscale, int half,
-                                                          int c12, char* out) {
-  const int cb = blockIdx.x * blockDim.x + threadIdx.x;
-  const int padded = ceil_div(half, kWave) * kWave;
-  if (cb >= padded) return;
-  const long blk = cb >> 6;
-  const int lane = cb & 63;
-  const float scale[2] = {lscale[blk * 2 * kWave + lane], lscale[blk * 2 * kWave + kWave + lane]};
-  for (int k = 0; k < kLinks; ++k) {
-    const bool two_rows = c12 && ((k & 3) >= 2);
-    const double2* in = reinterpret_cast<const double2*>(packed64 + link_slot_offset(P64, c12, blk, k)) + lane;
-    double2 u[9];
-#pragma unroll
-    for (int e = 0; e < 9; ++e) u[e] = e < (two_rows ? 6 : 9) ? in[e * kWave] : make_double2(0.0, 0.0);
-    const float sc = scale[(k >> 1) & 1];
-    h2v h[9];
-#pragma unroll
-    for (int e = 0; e < 9; ++e) {
-      h[e].x = f16_code(u[e].x, sc);
-      h[e].y = f16_code(u[e].y, sc);
-    }
-    char* base = out + link_slot_offset(P16, c12, blk, k);
-    uint4* o = reinterpret_cast<uint4*>(base) + lane;
-    if (two_rows) {
-      o[0] = make_uint4(__builtin_bit_cast(unsigned, h[0]), __builtin_bit_cast(unsigned, h[1]),
-                        __builtin_bit_cast(unsigned, h[2]), __builtin_bit_cast(unsigned, h[3]));
-      reinterpret_cast<uint2*>(base + kWave * 16)[lane] =
-          make_uint2(__builtin_bit_cast(unsigned, h[4]), __builtin_bit_cast(unsigned, h[5]));
-    } else {
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        o[j * kWave] = make_uint4(__builtin_bit_cast(unsigned, h[4 * j]), __builtin_bit_cast(unsigned, h[4 * j + 1]),
-                                  __builtin_bit_cast(unsigned, h[4 * j + 2]), __builtin_bit_cast(unsigned, h[4 * j + 3]));
-      reinterpret_cast<unsigned*>(base + 2 * kWave * 16)[lane] = __builtin_bit_cast(unsigned, h[8]);
-    }
-  }
-}
-
-hipError_t launch_pack_f16_from_f64(const void* packed64, const float* lscale, const Geo& g, void* out,
-                                    hipStream_t st) {
-  const int padded = ceil_div(g.half, kWave) * kWave;
-  k_pack_f16_from_f64<<<ceil_div(padded, 256), 256, 0, st>>>(reinterpret_cast<const char*>(packed64), lscale, g.half,
-                                                             g.long12, reinterpret_cast<char*>(out));
-  return hipGetLastError();
-}
-
-hipError_t launch_pack_links(int prec, const void* fat, const void* lng, double naik, const Geo& g, int antiper,
-                             int par, void* out, float* lscale, hipStream_t st) {
-  const int padded = ceil_div(g.half, kWave) * kWave;
-  const int nblk = ceil_div(padded, 256);
+hipError_t launch_pack_links(const void* fat, const void* lng, double naik, const Geo& g, const PackOut& out,
+                             hipStream_t st) {
+  const int nblk = ceil_div(g.half, kWave);
   auto f = reinterpret_cast<const double2*>(fat);
   auto l = reinterpret_cast<const double2*>(lng);
-  auto o = reinterpret_cast<char*>(out);
-  switch (prec) {
-    case P64: k_pack_links<P64><<<nblk, 256, 0, st>>>(f, l, naik, g, antiper, par, o, lscale); break;
-    case P32: k_pack_links<P32><<<nblk, 256, 0, st>>>(f, l, naik, g, antiper, par, o, lscale); break;
-    default: return hipErrorInvalidValue;
-  }
+  const bool w32 = out.f32[0] != nullptr, w16 = out.f16[0] != nullptr;
+  if (w32 && w16)
+    k_pack_links<true, true><<<nblk, 4 * kWave, 0, st>>>(f, l, naik, g, out);
+  else if (w32)
+    k_pack_links<true, false><<<nblk, 4 * kWave, 0, st>>>(f, l, naik, g, out);
+  else if (w16)
+    k_pack_links<false, true><<<nblk, 4 * kWave, 0, st>>>(f, l, naik, g, out);
+  else
+    k_pack_links<false, false><<<nblk, 4 * kWave, 0, st>>>(f, l, naik, g, out);
   return hipGetLastError();
 }
 

@@ -675,3 +675,34 @@ def test_dslash_f16_subnormal_site_scales(gpu_lib, long_su3):
             outs.append(out)
         assert np.array_equal(outs[0], outs[1]), par
     lat.set_dslash_shape("f16", 8, 0, 1)
+
+
+@pytest.mark.parametrize("dims", [(2, 2, 2, 2), (6, 4, 4, 6), (4, 6, 10, 2)])
+@pytest.mark.parametrize("storage", ["18 reals", "two rows", "no long links", "zero fat links"])
+def test_packing_together_is_packing_alone(gpu_lib, dims, storage):
+    """One pass packs every requested precision: each gives the operator it gives when packed alone, bit for
+    bit, on blocks with a ragged tail (8, 288 and 240 sites per parity), with and without long links, and with
+    a group of zero matrices (a zero FP16 scale)."""
+    from paper_1010_4782_amd.stagcg import Lattice
+
+    print(f"packing {dims} {storage}", flush=True)
+    fat = torch.from_numpy(fat_field(dims, 61)).cuda()
+    if storage == "zero fat links":
+        fat.zero_()
+    lng = None if storage == "no long links" else torch.from_numpy(random_su3_field(dims, 62)).cuda()
+    v = torch.from_numpy(gaussian_source(dims, 63, 2)).cuda()
+    kw = dict(long_su3=storage == "two rows")
+    both, alone = Lattice(dims), Lattice(dims)
+    both.load_links(fat, lng, NAIK, precs=("f64", "f32", "f16"), **kw)
+    ref = None
+    for prec in ("f64", "f32", "f16"):
+        alone.load_links(fat, lng, NAIK, precs=(prec,), **kw)
+        for par in (0, 1):
+            a, b = both.dslash(v, par, prec=prec), alone.dslash(v, par, prec=prec)
+            assert torch.equal(a, b), (prec, par)
+            if prec == "f64" and par == 0:
+                ref = a
+            # 16 matrices x 3 products of entries each within 2^-11 (binary16, link and vector) of the group's scale
+            tol = {"f64": 0.0, "f32": 48 * 3 * 2.0**-24, "f16": 48 * 3 * 2.0**-11}[prec]
+            if par == 0:
+                assert torch.max(torch.abs(a - ref)) <= tol * torch.max(torch.abs(v)) + 0.0
