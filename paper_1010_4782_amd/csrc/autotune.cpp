@@ -38,18 +38,43 @@ int rhs_divisor(const BatchHost& bh) {
   return r;
 }
 
-// Without a tuned entry: the XCD z-block order where the lattice allows it (else the lattice order),
-// and the best measured shape on the large lattices: 64-site workgroups with up to 4 RHS per lane, or,
-// for FP16 with 18-real three-hop links (no third-row rebuild, so 8 RHS fit a lane's registers),
-// 128-site workgroups with up to 8.
+// The colour vectors of one time slice, all right-hand sides, of the largest lattice.
+double slice_bytes(const BatchHost& bh, int prec) {
+  double m = 0.0;
+  for (const auto& p : bh.probs)
+    if (p.lt > 0) m = std::max(m, (double)(p.half / p.lt) * p.nrhs * spinor_bytes(prec));
+  return m;
+}
+
+// Without a tuned entry.  64-site workgroups (128 for FP16 at 8 RHS per lane); every choice gives the same bits.
+//  * Right-hand sides per lane: up to 4, where a lane's registers still leave two or three waves per SIMD; 8 for
+//    FP16 with 18-real three-hop links (no third-row rebuild), and for FP32 and FP64 from 2^18 sites of one
+//    parity on, where reading each link once is worth the one wave per SIMD it leaves (28^3x96 x 8: FP64 778 us
+//    against 929 at 4, FP32 376 and 444; 24^3x48: 259 and 261, 129 and 134; at 16^3x32 4 is faster, 45 us).
+//  * Fewer while that leaves less than two waves per SIMD (16^3x32 x 4: FP64 30 us at 2 per lane, 33 at 4).
+//  * Tile order: on a small lattice the lattice order, whose t neighbours are in an XCD's 4 MiB L2 anyway
+//    (16^3x32 x 8, FP64: 45 us, the z-block order 51).  From 2 MiB of colour vectors per time slice the orders
+//    that sweep t through one XCD's share: z blocks where the lattice allows them (32^3x64 x 8: FP64 781 us
+//    against 989, FP32 415 and 462), else the XCD sweep (28^3x96: FP64 x 12 RHS, 6.3 MB a slice, 1154 us against
+//    1398; FP32 x 8, 2.1 MB, 591 and 626; at 2.0 MB, 24^3x48 FP32 x 12, 264 and 260).  FP32 and FP64 take z blocks
+//    from 2^18 sites on (32^3x64 x 1: 349 us against 356 and 175 against 183; FP16 x 2: 108 against 103).
 DslashShape heuristic(const BatchHost& bh, int prec) {
+  constexpr int kLargeHalf = 1 << 18;
+  const bool r8_f16 = prec == P16 && !bh.long12, large = bh.max_half >= kLargeHalf;
+  const bool sweep = slice_bytes(bh, prec) >= 2.0 * 1024 * 1024;
   DslashShape s;
-  const bool r8 = prec == P16 && !bh.long12;
-  s.r = std::min(rhs_divisor(bh), r8 ? 8 : 4);
-  s.wg = r8 && s.r == 8 ? 128 : 64;
-  s.order = 1;
-  if (!dslash_shape_valid(bh, prec, s)) s.order = 0;
+  s.r = std::min(rhs_divisor(bh), r8_f16 || (prec != P16 && large) ? 8 : 4);
+  auto waves = [&](int r) {
+    long n = 0;
+    for (const auto& p : bh.probs) n += (long)ceil_div(p.half, kWave) * (p.nrhs / r);
+    return n;
+  };
+  while (s.r > 1 && waves(s.r) < 2048) s.r >>= 1;
+  s.wg = prec == P16 && s.r == 8 ? 128 : 64;
+  s.order = sweep || (prec != P16 && large) ? 1 : 0;
+  if (s.order && !dslash_shape_valid(bh, prec, s)) s.order = 0;
   if (!dslash_shape_valid(bh, prec, s)) s = DslashShape{64, 1, 0, 0};
+  s.sweep = s.order == 0 && sweep;
   return s;
 }
 

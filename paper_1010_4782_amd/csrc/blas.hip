@@ -574,35 +574,52 @@ hipError_t launch_finalize(const BatchHost& bh, int what, int kind, int gate, in
 
 // Time-slice sums for the pion correlator of point-source propagators:
 //   out[g][t] = (accumulate ? out[g][t] : 0) + weight * sum_{r in group g} sum_{i < slice} |v_r(t * slice + i)|^2
+//               + (n2 ? sum_{r in group g} sum_{i < slice} n2_r(t * slice + i) : 0)
 // The sites of one time slice and parity are the contiguous even-odd range [t * slice, (t + 1) * slice).
 // One workgroup per (group, slice) sums its slice in a fixed order: the result does not depend on the
-// launch.  FP64 colour vectors.
-__global__ __launch_bounds__(kMaxWG) void k_slice_norm2(const char* v, long half, int slice, int lt, int group,
-                                                        double weight, int accumulate, double* out) {
-  __shared__ double lds[4];
+// launch.  FP64.  A slice is read as plain 16-byte words, 16 waves with four words each in flight: there are
+// only as many workgroups as slices and groups (28^3x96, 4 groups of 3: 606 MB in @@ us; four waves reading
+// one 48-byte vector at a time took 164).
+constexpr int kSliceWG = 1024;
+__global__ __launch_bounds__(kSliceWG) void k_slice_norm2(const char* v, const double* n2, long half, int slice,
+                                                          int lt, int group, double weight, int accumulate,
+                                                          double* out) {
+  __shared__ double lds[2 * (kSliceWG / kWave)];
   const int t = blockIdx.x % lt, g = blockIdx.x / lt;
-  double acc[1] = {0.0};
+  double acc[2] = {0.0, 0.0};
+  const long words = 3L * slice;
   for (int r = 0; r < group; ++r) {
-    const char* base = v + (long)(g * group + r) * half * spinor_bytes(P64);
-    for (int i = threadIdx.x; i < slice; i += blockDim.x) {
-      Cx<double> c[3];
-      load_spinor<P64, true>(base, (long)t * slice + i, c);
+    const long first = (long)(g * group + r) * half + (long)t * slice;
+    gptr<d2v> p = as_global<d2v>(v) + 3 * first;
+    long i = threadIdx.x;
+    for (; i + 3 * kSliceWG < words; i += 4 * kSliceWG) {
+      d2v w[4];
 #pragma unroll
-      for (int k = 0; k < 3; ++k) acc[0] += c[k].re * c[k].re + c[k].im * c[k].im;
+      for (int k = 0; k < 4; ++k) w[k] = __builtin_nontemporal_load(p + i + k * kSliceWG);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[0] += w[k].x * w[k].x + w[k].y * w[k].y;
+    }
+    for (; i < words; i += kSliceWG) {
+      const d2v w = __builtin_nontemporal_load(p + i);
+      acc[0] += w.x * w.x + w.y * w.y;
+    }
+    if (n2) {
+      gptr<double> q = as_global<double>(n2) + first;
+      for (int k = threadIdx.x; k < slice; k += kSliceWG) acc[1] += q[k];
     }
   }
-  block_sum<1>(acc, lds);
+  block_sum<2, kSliceWG / kWave>(acc, lds);
   if (threadIdx.x == 0) {
-    const double val = weight * acc[0];
+    const double val = weight * acc[0] + acc[1];
     out[blockIdx.x] = accumulate ? out[blockIdx.x] + val : val;
   }
 }
 
-hipError_t launch_slice_norm2(const void* v, long half, int slice, int lt, int ngroups, int group, double weight,
-                              int accumulate, double* out, hipStream_t st) {
+hipError_t launch_slice_norm2(const void* v, const double* n2, long half, int slice, int lt, int ngroups, int group,
+                              double weight, int accumulate, double* out, hipStream_t st) {
   if (ngroups == 0) return hipSuccess;
-  k_slice_norm2<<<ngroups * lt, kMaxWG, 0, st>>>(reinterpret_cast<const char*>(v), half, slice, lt, group, weight,
-                                                 accumulate, out);
+  k_slice_norm2<<<ngroups * lt, kSliceWG, 0, st>>>(reinterpret_cast<const char*>(v), n2, half, slice, lt, group,
+                                                   weight, accumulate, out);
   return hipGetLastError();
 }
 

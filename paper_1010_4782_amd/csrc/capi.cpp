@@ -154,42 +154,102 @@ stag_status ring_release(Ctl& c, const RingEntry& e, hipStream_t st) {
   return STAG_OK;
 }
 
-// Set up a single-problem batch whose table, scalars and partials live in a ring entry.
-stag_status single_batch(stag_lattice_s* L, int nrhs, const double* mass, void* const* vec_override, hipStream_t st,
-                         BatchHost& bh, RingEntry& e, const Geo* geo_override = nullptr) {
-  const int pstride = ceil_div(L->g.half, kWave / 2);  // 32-site partials of the time-streaming kernel
-  const size_t off_scal = (sizeof(ProbDev) + 255) & ~size_t(255);
-  const size_t off_part = off_scal + ((sizeof(Scal) * nrhs + 255) & ~size_t(255));
-  const size_t need = off_part + sizeof(double) * (size_t)nrhs * kPartialSlots * pstride;
-  stag_status s = ring_acquire(L->ctl, need, e);
-  if (s != STAG_OK) return s;
+// The problem of an operator call: the lattice with the vectors of `vec_override`, or a slab of it.
+ProbDev op_problem(const stag_lattice_s* L, int nrhs, void* const* vec_override, const Geo* geo_override) {
   ProbDev pd = prob_dev(L, nrhs, 0);
   if (geo_override) pd.g = *geo_override;
-  for (int v = 0; v < kNumVec; ++v) pd.vec[v] = L->vec[v].ptr;
-  for (int v = 0; v < kNumVec; ++v)
-    if (vec_override[v]) pd.vec[v] = vec_override[v];
+  for (int v = 0; v < kNumVec; ++v) pd.vec[v] = vec_override[v] ? vec_override[v] : L->vec[v].ptr;
+  return pd;
+}
+void op_sizes(const ProbDev& pd, BatchHost& bh) {
+  bh.probs.assign(1, HostProb{pd.g.half, pd.nrhs, 0, pd.g.Xh, pd.g.L[1], pd.g.L[2], pd.g.L[3], pd.g.t_open});
+  bh.pstride = 0;  // the epilogues of operator calls write no partial sums
+  bh.nslots = pd.nrhs;
+  bh.max_half = pd.g.half;
+  bh.long12 = pd.g.long12 != 0;
+}
+
+// Put the problem's table and scalars into a ring entry in device memory.
+stag_status ring_batch(stag_lattice_s* L, const ProbDev& pd, const double* mass, hipStream_t st, BatchHost& bh,
+                       RingEntry& e) {
+  const size_t off_scal = (sizeof(ProbDev) + 255) & ~size_t(255);
+  const size_t need = off_scal + sizeof(Scal) * pd.nrhs;
+  stag_status s = ring_acquire(L->ctl, need, e);
+  if (s != STAG_OK) return s;
   std::memcpy(e.host, &pd, sizeof(pd));
   Scal* sc = reinterpret_cast<Scal*>(e.host + off_scal);
-  for (int r = 0; r < nrhs; ++r) {
+  for (int r = 0; r < pd.nrhs; ++r) {
     Scal z{};
     z.mass4 = mass ? 4.0 * mass[r] * mass[r] : 0.0;
     sc[r] = z;
   }
-  STAG_HIP_TRY(hipMemcpyAsync(e.dev, e.host, off_part, hipMemcpyHostToDevice, st));
-  bh.probs.assign(1, HostProb{pd.g.half, nrhs, 0, pd.g.Xh, pd.g.L[1], pd.g.L[2], pd.g.L[3], pd.g.t_open});
+  STAG_HIP_TRY(hipMemcpyAsync(e.dev, e.host, need, hipMemcpyHostToDevice, st));
   bh.d_probs = reinterpret_cast<const ProbDev*>(e.dev);
   bh.d_scal = reinterpret_cast<Scal*>(e.dev + off_scal);
-  bh.d_partial = reinterpret_cast<double*>(e.dev + off_part);
-  bh.pstride = pstride;
-  bh.nslots = nrhs;
-  bh.max_half = pd.g.half;
-  bh.long12 = L->g.long12 != 0;
+  bh.d_partial = nullptr;
   return STAG_OK;
 }
 
 std::string single_key(const BatchHost& bh, const stag_lattice_s* L, int prec) {
   std::vector<const stag_lattice_s*> lats{L};
   return tune_key(bh, lats, prec);
+}
+
+// An operator call: its batch and launch shape.  Up to kInlineRhs right-hand sides travel in the kernel
+// arguments; more of them, and the time-streaming kernel, read a table in a ring entry that a copy fills first
+// (at 8^4 that copy and its event were half of the call).
+struct OpCall {
+  BatchHost bh;
+  ProbDev pd;
+  DslashShape sh;
+  RingEntry e{};
+  bool ring = false;
+};
+stag_status op_begin(stag_lattice_s* L, int nrhs, const double* mass, void* const* vec_override, int prec,
+                     hipStream_t st, OpCall& c, const Geo* geo_override = nullptr) {
+  c.pd = op_problem(L, nrhs, vec_override, geo_override);
+  op_sizes(c.pd, c.bh);
+  c.sh = lookup_shape(c.bh, single_key(c.bh, L, prec), prec);
+  c.ring = nrhs > kInlineRhs || c.sh.order == 2;
+  if (c.ring) return ring_batch(L, c.pd, mass, st, c.bh, c.e);
+  c.bh.inl = &c.pd;
+  c.bh.inl_mass = mass;
+  return STAG_OK;
+}
+stag_status op_end(stag_lattice_s* L, const OpCall& c, hipStream_t st) {
+  return c.ring ? ring_release(L->ctl, c.e, st) : STAG_OK;
+}
+
+// out = D in for complex128 fields of in_sites and out_sites sites per right-hand side, the first output site
+// reading its own position at in + first.  FP32 and FP16 round the input to storage first; the operator writes
+// its rounded result widened, except for the time-streaming shape, whose stored output a second pass widens.
+stag_status low_or_full_dslash(stag_lattice_s* lat, int out_parity, const void* in, long in_sites, void* out,
+                               long out_sites, long first, int nrhs, int prec, const Geo* geo, hipStream_t st) {
+  void* ov[kNumVec] = {};
+  const size_t vb = spinor_bytes(prec);
+  ov[V_D] = const_cast<char*>(static_cast<const char*>(in)) + first * vb;
+  ov[V_T] = out;
+  if (prec != STAG_F64) {
+    STAG_HIP_TRY(lat->io_lo[0].ensure(vb * in_sites * nrhs));
+    STAG_HIP_TRY(launch_convert_from_f64(prec, in, lat->io_lo[0].ptr, in_sites * nrhs, st));
+    ov[V_D] = static_cast<char*>(lat->io_lo[0].ptr) + first * vb;
+  }
+  OpCall c;
+  stag_status s = op_begin(lat, nrhs, nullptr, ov, prec, st, c, geo);
+  if (s != STAG_OK) return s;
+  if (c.sh.order == 2) {
+    STAG_HIP_TRY(lat->io_lo[1].ensure(vb * out_sites * nrhs));
+    // the table is already on its way: point it at the low-precision output
+    ov[V_T] = lat->io_lo[1].ptr;
+    s = op_end(lat, c, st);
+    if (s == STAG_OK) s = op_begin(lat, nrhs, nullptr, ov, prec, st, c, geo);
+    if (s != STAG_OK) return s;
+  }
+  const bool wide = prec != STAG_F64 && c.sh.order != 2;
+  STAG_HIP_TRY(launch_dslash(c.bh, prec, wide ? EPI_WIDE : EPI_PLAIN, out_parity, V_D, V_T, 0, 0, 3, c.sh, st));
+  if (prec != STAG_F64 && !wide)
+    STAG_HIP_TRY(launch_convert_to_f64(prec, lat->io_lo[1].ptr, out, out_sites * nrhs, st));
+  return op_end(lat, c, st);
 }
 
 stag_status check_lattice(stag_lattice_t lat) {
@@ -332,26 +392,7 @@ stag_status stag_dslash(stag_lattice_t lat, int32_t out_parity, const void* in, 
   if (prec < STAG_F64 || prec > STAG_F16) return arg_error("prec must be STAG_F64, STAG_F32 or STAG_F16");
   if (!(lat->built & STAG_PREC_BIT(prec))) return arg_error("the requested precision was not packed by load_links");
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  void* ov[kNumVec] = {};
-  const long nsites = (long)lat->g.half * nrhs;
-  if (prec == STAG_F64) {
-    ov[V_D] = const_cast<void*>(in);
-    ov[V_T] = out;
-  } else {
-    STAG_HIP_TRY(lat->io_lo[0].ensure(spinor_field_bytes(lat, prec, nrhs)));
-    STAG_HIP_TRY(lat->io_lo[1].ensure(spinor_field_bytes(lat, prec, nrhs)));
-    STAG_HIP_TRY(launch_convert_from_f64(prec, in, lat->io_lo[0].ptr, nsites, st));
-    ov[V_D] = lat->io_lo[0].ptr;
-    ov[V_T] = lat->io_lo[1].ptr;
-  }
-  BatchHost bh;
-  RingEntry e;
-  s = single_batch(lat, nrhs, nullptr, ov, st, bh, e);
-  if (s != STAG_OK) return s;
-  const DslashShape sh = lookup_shape(bh, single_key(bh, lat, prec), prec);
-  STAG_HIP_TRY(launch_dslash(bh, prec, EPI_PLAIN, out_parity, V_D, V_T, 0, 0, 3, sh, st));
-  if (prec != STAG_F64) STAG_HIP_TRY(launch_convert_to_f64(prec, lat->io_lo[1].ptr, out, nsites, st));
-  return ring_release(lat->ctl, e, st);
+  return low_or_full_dslash(lat, out_parity, in, lat->g.half, out, lat->g.half, 0, nrhs, prec, nullptr, st);
   STAG_GUARD_END
 }
 
@@ -384,27 +425,8 @@ stag_status stag_dslash_slab(stag_lattice_t lat, int32_t out_parity, int32_t t0,
   gs.h3[3] = 3;
   gs.t0 = t0;
   gs.t_open = 1;
-  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  void* ov[kNumVec] = {};
-  const size_t vb = spinor_bytes(prec);
-  if (prec == STAG_F64) {
-    ov[V_D] = const_cast<char*>(static_cast<const char*>(in_ext)) + 3 * slice * vb;  // first interior slice
-    ov[V_T] = out;
-  } else {
-    STAG_HIP_TRY(lat->io_lo[0].ensure(vb * in_sites * nrhs));
-    STAG_HIP_TRY(lat->io_lo[1].ensure(vb * out_sites * nrhs));
-    STAG_HIP_TRY(launch_convert_from_f64(prec, in_ext, lat->io_lo[0].ptr, in_sites * nrhs, st));
-    ov[V_D] = static_cast<char*>(lat->io_lo[0].ptr) + 3 * slice * vb;
-    ov[V_T] = lat->io_lo[1].ptr;
-  }
-  BatchHost bh;
-  RingEntry e;
-  s = single_batch(lat, nrhs, nullptr, ov, st, bh, e, &gs);
-  if (s != STAG_OK) return s;
-  const DslashShape sh = lookup_shape(bh, single_key(bh, lat, prec), prec);
-  STAG_HIP_TRY(launch_dslash(bh, prec, EPI_PLAIN, out_parity, V_D, V_T, 0, 0, 3, sh, st));
-  if (prec != STAG_F64) STAG_HIP_TRY(launch_convert_to_f64(prec, lat->io_lo[1].ptr, out, out_sites * nrhs, st));
-  return ring_release(lat->ctl, e, st);
+  return low_or_full_dslash(lat, out_parity, in_ext, in_sites, out, out_sites, 3 * slice, nrhs, prec, &gs,
+                            reinterpret_cast<hipStream_t>(stream));
   STAG_GUARD_END
 }
 
@@ -423,14 +445,12 @@ stag_status stag_apply_m(stag_lattice_t lat, const double* mass, const void* in,
   void* ov[kNumVec] = {};
   ov[V_D] = const_cast<void*>(in);
   ov[V_AD] = out;
-  BatchHost bh;
-  RingEntry e;
-  s = single_batch(lat, nrhs, mass, ov, st, bh, e);
+  OpCall c;
+  s = op_begin(lat, nrhs, mass, ov, P64, st, c);
   if (s != STAG_OK) return s;
-  const DslashShape sh = lookup_shape(bh, single_key(bh, lat, P64), P64);
-  STAG_HIP_TRY(launch_dslash(bh, P64, EPI_PLAIN, 1, V_D, V_TMPO, 0, 0, 3, sh, st));
-  STAG_HIP_TRY(launch_dslash(bh, P64, EPI_XPAY, 0, V_TMPO, V_AD, V_D, 0, 3, sh, st));
-  return ring_release(lat->ctl, e, st);
+  STAG_HIP_TRY(launch_dslash(c.bh, P64, EPI_PLAIN, 1, V_D, V_TMPO, 0, 0, 3, c.sh, st));
+  STAG_HIP_TRY(launch_dslash(c.bh, P64, EPI_XPAY, 0, V_TMPO, V_AD, V_D, 0, 3, c.sh, st));
+  return op_end(lat, c, st);
   STAG_GUARD_END
 }
 
@@ -504,7 +524,7 @@ stag_status stag_slice_norm2(stag_lattice_t lat, const void* v, int32_t nrhs, in
   if (!std::isfinite(weight)) return arg_error("weight must be finite");
   if (accumulate != 0 && accumulate != 1) return arg_error("accumulate must be 0 or 1");
   const int lt = lat->dims[3];
-  STAG_HIP_TRY(launch_slice_norm2(v, lat->g.half, lat->g.half / lt, lt, nrhs / group, group, weight, accumulate, out,
+  STAG_HIP_TRY(launch_slice_norm2(v, nullptr, lat->g.half, lat->g.half / lt, lt, nrhs / group, group, weight, accumulate, out,
                                   reinterpret_cast<hipStream_t>(stream)));
   return STAG_OK;
   STAG_GUARD_END
@@ -520,22 +540,21 @@ stag_status stag_pion_correlator(stag_lattice_t lat, const void* chi, int32_t ns
   if (!std::isfinite(mass)) return arg_error("mass must be finite");
   const int nrhs = 3 * nsrc;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  STAG_HIP_TRY(lat->vec[V_TMPO].ensure(spinor_field_bytes(lat, P64, nrhs)));
+  // |D_oe chi|^2 = |G_o|^2 (the sign of G_o does not enter), one number per site
+  STAG_HIP_TRY(lat->vec[V_TMPO].ensure((size_t)lat->g.half * sizeof(double) * nrhs));
   void* ov[kNumVec] = {};
   ov[V_D] = const_cast<void*>(chi);
-  BatchHost bh;
-  RingEntry e;
-  s = single_batch(lat, nrhs, nullptr, ov, st, bh, e);
+  OpCall c;
+  s = op_begin(lat, nrhs, nullptr, ov, P64, st, c);
   if (s != STAG_OK) return s;
-  const DslashShape sh = lookup_shape(bh, single_key(bh, lat, P64), P64);
-  STAG_HIP_TRY(launch_dslash(bh, P64, EPI_PLAIN, 1, V_D, V_TMPO, 0, 0, 3, sh, st));
-  s = ring_release(lat->ctl, e, st);
+  STAG_HIP_TRY(launch_dslash(c.bh, P64, EPI_NORM, 1, V_D, V_TMPO, 0, 0, 3, c.sh, st));
+  s = op_end(lat, c, st);
   if (s != STAG_OK) return s;
   const int lt = lat->dims[3];
   const long half = lat->g.half;
-  // |D_oe chi|^2 = |G_o|^2 (the sign of G_o does not enter); the even part carries (2m)^2
-  STAG_HIP_TRY(launch_slice_norm2(chi, half, half / lt, lt, nsrc, 3, 4.0 * mass * mass, 0, out, st));
-  STAG_HIP_TRY(launch_slice_norm2(lat->vec[V_TMPO].ptr, half, half / lt, lt, nsrc, 3, 1.0, 1, out, st));
+  // the even part carries (2m)^2
+  STAG_HIP_TRY(launch_slice_norm2(chi, static_cast<const double*>(lat->vec[V_TMPO].ptr), half, half / lt, lt, nsrc, 3,
+                                  4.0 * mass * mass, 0, out, st));
   return STAG_OK;
   STAG_GUARD_END
 }
@@ -572,7 +591,9 @@ stag_status stag_tune_dslash(stag_lattice_t lat, int32_t prec, int32_t nrhs, sta
   void* ov[kNumVec] = {};
   BatchHost bh;
   RingEntry e;
-  s = single_batch(lat, nrhs, nullptr, ov, st, bh, e);
+  const ProbDev pd = op_problem(lat, nrhs, ov, nullptr);
+  op_sizes(pd, bh);
+  s = ring_batch(lat, pd, nullptr, st, bh, e);
   if (s != STAG_OK) return s;
   DslashShape b{};
   std::vector<std::pair<DslashShape, float>> timed;

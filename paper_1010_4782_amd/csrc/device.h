@@ -148,11 +148,36 @@ __device__ __forceinline__ void load_spinor_lds(const char* base, int s, float l
   }
 }
 
-// Store and return the stored (rounded) value in v.  FP16: code = binary16(v / m), m = max |component|;
-// RCP takes the six quotients as v x binary32(1 / m), one division per site instead of six (each
-// quotient then within 2^-23 of v / m, far below the binary16 rounding that follows): the Dslash
-// epilogues, where the divisions are a tenth of the arithmetic.  A subnormal m (the edge of a point
-// source's spreading support reaches 1e-39) keeps the six divisions: 1 / m would overflow.
+// The value v rounded to storage, in v.  FP16: code = binary16(v / m), m = max |component|, returned with the
+// codes in `code`; RCP takes the six quotients as v x binary32(1 / m), one division per site instead of six
+// (each quotient then within 2^-23 of v / m, far below the binary16 rounding that follows): the Dslash
+// epilogues, where the divisions are a tenth of the arithmetic.  A subnormal m (the edge of a point source's
+// spreading support reaches 1e-39) keeps the six divisions: 1 / m would overflow.
+template <bool RCP>
+__device__ __forceinline__ u4v round_spinor_f16(Cx<float> v[3]) {
+  float m = 0.f;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) m = fmaxf(m, fmaxf(fabsf(v[c].re), fabsf(v[c].im)));
+  unsigned w0 = 0u, w1 = 0u, w2 = 0u;
+  if (m > 0.f) {
+    if (RCP && m >= 0x1p-126f) {
+      const float inv = 1.f / m;
+      w0 = pack_h2(v[0].re * inv, v[0].im * inv);
+      w1 = pack_h2(v[1].re * inv, v[1].im * inv);
+      w2 = pack_h2(v[2].re * inv, v[2].im * inv);
+    } else {
+      w0 = pack_h2(v[0].re / m, v[0].im / m);
+      w1 = pack_h2(v[1].re / m, v[1].im / m);
+      w2 = pack_h2(v[2].re / m, v[2].im / m);
+    }
+  }
+  v[0] = unpack_h2(w0, m);
+  v[1] = unpack_h2(w1, m);
+  v[2] = unpack_h2(w2, m);
+  return u4v{w0, w1, w2, __float_as_uint(m)};
+}
+
+// Store and return the stored (rounded) value in v.
 template <int P, bool NT = false, bool RCP = false>
 __device__ __forceinline__ void store_spinor(void* base, long s, Cx<typename RealOf<P>::T> v[3]) {
   if constexpr (P == P64) {
@@ -164,26 +189,7 @@ __device__ __forceinline__ void store_spinor(void* base, long s, Cx<typename Rea
 #pragma unroll
     for (int c = 0; c < 3; ++c) st<f2v, NT>(p + c, f2v{v[c].re, v[c].im});
   } else {
-    float m = 0.f;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) m = fmaxf(m, fmaxf(fabsf(v[c].re), fabsf(v[c].im)));
-    unsigned w0 = 0u, w1 = 0u, w2 = 0u;
-    if (m > 0.f) {
-      if (RCP && m >= 0x1p-126f) {
-        const float inv = 1.f / m;
-        w0 = pack_h2(v[0].re * inv, v[0].im * inv);
-        w1 = pack_h2(v[1].re * inv, v[1].im * inv);
-        w2 = pack_h2(v[2].re * inv, v[2].im * inv);
-      } else {
-        w0 = pack_h2(v[0].re / m, v[0].im / m);
-        w1 = pack_h2(v[1].re / m, v[1].im / m);
-        w2 = pack_h2(v[2].re / m, v[2].im / m);
-      }
-    }
-    st<u4v, NT>(as_global_w<u4v>(base) + s, u4v{w0, w1, w2, __float_as_uint(m)});
-    v[0] = unpack_h2(w0, m);
-    v[1] = unpack_h2(w1, m);
-    v[2] = unpack_h2(w2, m);
+    st<u4v, NT>(as_global_w<u4v>(base) + s, round_spinor_f16<RCP>(v));
   }
 }
 
@@ -263,39 +269,30 @@ template <> struct RawLink<P64> { d2v e[9]; };
 template <> struct RawLink<P32> { f4v q[4]; f2v t; };
 template <> struct RawLink<P16> { u4v q0, q1; unsigned t; };
 
-template <int P, int ROWS> __device__ __forceinline__ void raw_link_load(const char* slot, int lane, RawLink<P>& r);
-template <> __device__ __forceinline__ void raw_link_load<P64, 3>(const char* slot, int lane, RawLink<P64>& r) {
-  gptr<d2v> p = as_global<d2v>(slot) + lane;
+// NT: non-temporal, for links that only this workgroup reads (they then take no L2 lines from the colour
+// vectors); ordinary loads where another workgroup reads the same links for other right-hand sides.
+template <int P, int ROWS, bool NT = true>
+__device__ __forceinline__ void raw_link_load(const char* slot, int lane, RawLink<P>& r) {
+  if constexpr (P == P64) {
+    gptr<d2v> p = as_global<d2v>(slot) + lane;
 #pragma unroll
-  for (int e = 0; e < 9; ++e) r.e[e] = __builtin_nontemporal_load(p + e * kWave);
-}
-template <> __device__ __forceinline__ void raw_link_load<P64, 2>(const char* slot, int lane, RawLink<P64>& r) {
-  gptr<d2v> p = as_global<d2v>(slot) + lane;
+    for (int e = 0; e < 3 * ROWS; ++e) r.e[e] = ld<d2v, NT>(p + e * kWave);
+  } else if constexpr (P == P32) {
+    gptr<f4v> p = as_global<f4v>(slot) + lane;
 #pragma unroll
-  for (int e = 0; e < 6; ++e) r.e[e] = __builtin_nontemporal_load(p + e * kWave);
-}
-template <> __device__ __forceinline__ void raw_link_load<P32, 3>(const char* slot, int lane, RawLink<P32>& r) {
-  gptr<f4v> p = as_global<f4v>(slot) + lane;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) r.q[j] = __builtin_nontemporal_load(p + j * kWave);
-  r.t = __builtin_nontemporal_load(as_global<f2v>(slot + 4 * kWave * 16) + lane);
-}
-template <> __device__ __forceinline__ void raw_link_load<P32, 2>(const char* slot, int lane, RawLink<P32>& r) {
-  gptr<f4v> p = as_global<f4v>(slot) + lane;
-#pragma unroll
-  for (int j = 0; j < 3; ++j) r.q[j] = __builtin_nontemporal_load(p + j * kWave);
-}
-template <> __device__ __forceinline__ void raw_link_load<P16, 3>(const char* slot, int lane, RawLink<P16>& r) {
-  gptr<u4v> p = as_global<u4v>(slot) + lane;
-  r.q0 = __builtin_nontemporal_load(p);
-  r.q1 = __builtin_nontemporal_load(p + kWave);
-  r.t = __builtin_nontemporal_load(as_global<unsigned>(slot + 2 * kWave * 16) + lane);
-}
-template <> __device__ __forceinline__ void raw_link_load<P16, 2>(const char* slot, int lane, RawLink<P16>& r) {
-  r.q0 = __builtin_nontemporal_load(as_global<u4v>(slot) + lane);
-  const u2v t = __builtin_nontemporal_load(as_global<u2v>(slot + kWave * 16) + lane);
-  r.q1.x = t.x;
-  r.q1.y = t.y;
+    for (int j = 0; j < ROWS + 1; ++j) r.q[j] = ld<f4v, NT>(p + j * kWave);
+    if constexpr (ROWS == 3) r.t = ld<f2v, NT>(as_global<f2v>(slot + 4 * kWave * 16) + lane);
+  } else if constexpr (ROWS == 3) {
+    gptr<u4v> p = as_global<u4v>(slot) + lane;
+    r.q0 = ld<u4v, NT>(p);
+    r.q1 = ld<u4v, NT>(p + kWave);
+    r.t = ld<unsigned, NT>(as_global<unsigned>(slot + 2 * kWave * 16) + lane);
+  } else {
+    r.q0 = ld<u4v, NT>(as_global<u4v>(slot) + lane);
+    const u2v t = ld<u2v, NT>(as_global<u2v>(slot + kWave * 16) + lane);
+    r.q1.x = t.x;
+    r.q1.y = t.y;
+  }
 }
 
 template <int P, int ROWS>

@@ -11,7 +11,9 @@ enum Epi : int {
   EPI_PLAIN = 0,     // out = D in
   EPI_XPAY_DOT = 1,  // out = 4m^2 x - D in ; partial[kind 0] = Re <x, out>
   EPI_RESID = 2,     // out = b - (4m^2 x - D in) ; partial[kind 1] = |out|^2   (FP64 only)
-  EPI_XPAY = 3       // out = 4m^2 x - D in                                      (FP64 only)
+  EPI_XPAY = 3,      // out = 4m^2 x - D in                                      (FP64 only)
+  EPI_WIDE = 4,      // out = D in rounded to storage, widened to FP64           (FP32 and FP16 only)
+  EPI_NORM = 5       // out = |D in|^2 per site, one double                      (FP64 only)
 };
 
 // Host mirror of a batch: sizes the launchers need to build the block map.
@@ -29,6 +31,8 @@ constexpr int kTGroupRhs = 8;  // right-hand sides per site of a time-streaming 
 
 constexpr size_t kMaxDslashLds = 64 * 1024;  // LDS a staged Dslash workgroup may use
 
+constexpr int kInlineRhs = 16;  // right-hand sides of a problem carried in the kernel arguments, at most
+
 struct BatchHost {
   std::vector<HostProb> probs;
   const ProbDev* d_probs = nullptr;
@@ -37,6 +41,8 @@ struct BatchHost {
   int pstride = 0;
   int nslots = 0;
   int max_half = 0;
+  const ProbDev* inl = nullptr;      // a single problem carried in the kernel arguments (host; d_probs unused)
+  const double* inl_mass = nullptr;  // its masses (host), for EPI_XPAY
   bool long12 = false;   // every lattice of the batch stores its three-hop links as two rows
 };
 
@@ -52,6 +58,7 @@ struct DslashShape {
                   // 2: the time-streaming FP16 kernel (dslash_t.hip): wg 64 (one wave), r 8 (one lane per
                   //    site) or r 4 (two lanes per site, 32 sites per wave)
   int chunks = 1; // order 2: the time extent is walked in this many chunks (one wave per chunk)
+  bool sweep = false;  // order 0 only: XCD sweep instead of the lattice order (same result); the untuned default
 };
 
 // Sites per reduction partial of the xpay launch of this shape (the finalize's producer_wg).
@@ -69,8 +76,10 @@ hipError_t launch_dslash_t(const BatchHost& bh, int epi, int out_par, int in_id,
 
 // Vector stages of the solvers (every one is one launch over all slots of the batch).
 hipError_t launch_norm2(const BatchHost& bh, int prec, int v_id, int kind, int gate, int wg, hipStream_t st);
-hipError_t launch_slice_norm2(const void* v, long half, int slice, int lt, int ngroups, int group, double weight,
-                              int accumulate, double* out, hipStream_t st);
+// out[g][t] (+)= weight sum |v|^2 over slice t of the group's right-hand sides, plus the sum of n2 [nrhs][V/2]
+// (one number per site; may be null) over the same slice and right-hand sides.
+hipError_t launch_slice_norm2(const void* v, const double* n2, long half, int slice, int lt, int ngroups, int group,
+                              double weight, int accumulate, double* out, hipStream_t st);
 // producer_wg: sites per block of the launch that wrote the first partial kind; aux_wg (0: the same)
 // for the further kinds of multi-kind modes.
 hipError_t launch_finalize(const BatchHost& bh, int what, int kind, int gate, int producer_wg, double* hist,

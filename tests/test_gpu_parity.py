@@ -706,3 +706,32 @@ def test_packing_together_is_packing_alone(gpu_lib, dims, storage):
             tol = {"f64": 0.0, "f32": 48 * 3 * 2.0**-24, "f16": 48 * 3 * 2.0**-11}[prec]
             if par == 0:
                 assert torch.max(torch.abs(a - ref)) <= tol * torch.max(torch.abs(v)) + 0.0
+
+
+# 18 RHS: the table in device memory (more than 16), FP64 in the XCD sweep (2.2 MB of colour vectors per time
+# slice); 16 RHS: the arguments' table, every precision in the sweep (2.8 to 8.4 MB); 2 and 3: the lattice order
+@pytest.mark.parametrize("dims,nrhs", [((20, 18, 14, 6), 18), ((28, 28, 28, 4), 16), ((6, 4, 4, 6), 3), ((2, 2, 2, 2), 2)])
+@pytest.mark.parametrize("su3", [False, True])
+def test_operator_calls_are_their_single_rhs_calls(gpu_lib, dims, nrhs, su3):
+    """Launch shapes, tile orders and argument paths chosen by size leave every right-hand side's bits alone."""
+    from paper_1010_4782_amd.stagcg import Lattice
+
+    print(f"operator calls {dims} x {nrhs} su3 {su3}", flush=True)
+    fat, lng = (torch.from_numpy(f(dims, 64 + i)).cuda() for i, f in enumerate((fat_field, random_su3_field)))
+    lat = Lattice(dims)
+    lat.load_links(fat, lng, NAIK, precs=("f64", "f32", "f16"), long_su3=su3)
+    v = torch.from_numpy(gaussian_source(dims, 66, nrhs)).cuda()
+    for prec in ("f64", "f32", "f16"):
+        for par in (0, 1):
+            out = lat.dslash(v, par, prec=prec)
+            for r in range(0, nrhs, 5):
+                assert torch.equal(out[r], lat.dslash(v[r:r + 1].contiguous(), par, prec=prec)[0]), (prec, par, r)
+    mass = [0.01 * (r + 1) for r in range(nrhs)]
+    mv = lat.apply_m(v, mass)
+    for r in range(0, nrhs, 5):
+        assert torch.equal(mv[r], lat.apply_m(v[r:r + 1].contiguous(), mass[r])[0]), r
+    if nrhs % 3 == 0:  # the correlator's fused norms against the operator's output: sums of positive terms
+        c = lat.pion_correlator(v, 0.07)
+        ref = lat.slice_norm2(v, 3, 4 * 0.07**2)
+        lat.slice_norm2(lat.dslash(v, 1), 3, 1.0, out=ref, accumulate=True)
+        assert torch.max(torch.abs(c - ref) / ref) <= 2 * 3 * 6 * dims[0] * dims[1] * dims[2] * 2.0**-53
