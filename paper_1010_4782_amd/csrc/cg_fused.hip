@@ -1,4 +1,4 @@
-// CG iterations of small problems with the scalar steps inside the vector kernels.
+// CG iterations with the scalar steps inside the vector kernels.
 //
 // On a small lattice an iteration of the general path (Dslash, Dslash + <d, Ad>, finalize, r update,
 // finalize, x and d update) is six launches of 3.3-6 us that each wait on a chain of memory round trips; the
@@ -57,10 +57,11 @@ __device__ __forceinline__ const double* partials(const Batch& B, int slot, int 
   return B.partial + ((long)slot * kPartialSlots + kind) * B.pstride;
 }
 
-// Beta and the stopping test of a slot (k_finalize's FIN_BETA).  Returns the state after it (2 if the slot was
-// not running) and beta; the workgroup of tile 0 writes the slot's scalars to the other bank.
+// Beta and the stopping test of a slot (k_finalize's FIN_BETA); r2() gives |r|^2.  Returns the state after it
+// (2 if the slot was not running) and beta; the workgroup of tile 0 writes the slot's scalars to the other bank.
+template <typename Sum>
 __device__ __forceinline__ int beta_step(const Batch& B, const Slot& m, Scal* next, double* hist, int hist_stride,
-                                         double* lds, double& beta) {
+                                         Sum&& r2, double& beta) {
   const Scal& pre = B.scal[m.slot];
   const int st = pre.state;
   const double delta0 = pre.delta, thr0 = pre.thr, rel0 = pre.rel_thr;
@@ -69,7 +70,7 @@ __device__ __forceinline__ int beta_step(const Batch& B, const Slot& m, Scal* ne
   int now = st, flags = pre.flags;
   beta = 0.0;
   if (st == 0) {  // uniform
-    sum = sum_partials(partials(B, m.slot, 1), ceil_div(m.pd->g.half, kMaxWG), lds);
+    sum = r2();
     if (!isfinite(sum)) {
       now = 2;
       flags |= kFlagNaN;
@@ -179,7 +180,9 @@ __global__ __launch_bounds__(kMaxWG) void k_xd(Batch B, Scal* next, int x_id, in
   const int cb = m.tile * kMaxWG + threadIdx.x;
   const TX alpha = (TX)B.scal[m.slot].alpha;
   double b64;
-  const int now = beta_step(B, m, next, hist, hist_stride, lds, b64);
+  const int now = beta_step(
+      B, m, next, hist, hist_stride,
+      [&] { return sum_partials(partials(B, m.slot, 1), ceil_div(half, kMaxWG), lds); }, b64);
   if (now > 1 || cb >= half) return;
   const T beta = (T)b64;
   char* dp = reinterpret_cast<char*>(m.pd->vec[V_D]) + (long)m.r * half * spinor_bytes(P);
@@ -200,36 +203,239 @@ __global__ __launch_bounds__(kMaxWG) void k_xd(Batch B, Scal* next, int x_id, in
   store_spinor<P, kNT>(dp, cb, d);
 }
 
+// ---- larger problems ----------------------------------------------------------------------------------
+// With more partials the same two kernels run as one 1024-lane workgroup per CU at most: each adds all partials
+// of its slot, lane t the partials t, t + 1024, ... as k_finalize does, then walks its share of the slot's
+// vectors.  Such a launch reads the partials once per workgroup (24^3x48: 41 KB, 10 MB in all, from L2) while its
+// first sites are on their way, where the general path waits for a one-workgroup launch (6.4 us) twice an
+// iteration.  An iteration takes, general -> wide: 24^3x48 FP16 112.8 -> 106.2 us, FP64 272 -> 266; 20^3x40 x 4
+// FP16 123.1 -> 115.9; 32^3x64 FP32 497 -> 490; 28^3x96 FP16 270.1 -> 267.9.  With 512 workgroups the sums cost
+// more than the second workgroup per CU gives: 109.9 us (24^3x48 FP16), 274.5 (28^3x96).
+constexpr int kWideWG = 1024;
+constexpr int kWideGrid = 256;    // one per CU
+constexpr int kWideUnroll = 24;   // partials a lane has in flight
+
+__device__ __forceinline__ double wide_sum(const double* src, int n, double* lds /* >= 16 */) {
+  double s[1] = {0.0};
+  for (int base = 0; base < n; base += kWideUnroll * kWideWG) {
+    double v[kWideUnroll];
+#pragma unroll
+    for (int j = 0; j < kWideUnroll; ++j) {
+      const int i = base + j * kWideWG + threadIdx.x;
+      v[j] = i < n ? src[i] : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < kWideUnroll; ++j) s[0] += v[j];
+  }
+  wave_sum<1>(s);
+  if (threadIdx.x % kWave == 0) lds[threadIdx.x / kWave] = s[0];
+  __syncthreads();
+  double t = lds[0];
+  for (int w = 1; w < kWideWG / kWave; ++w) t += lds[w];
+  return t;
+}
+
+// Workgroup of a wide launch: B.groups[p] workgroups per slot of problem p; `tile` is this one's number.
+__device__ __forceinline__ Slot wide_slot(const Batch& B) {
+  Slot m;
+  const int p = find_problem(B, blockIdx.x);
+  m.pd = B.probs + p;
+  const int local = blockIdx.x - B.block_start[p], groups = B.groups[p];
+  m.r = local / groups;
+  m.tile = local - m.r * groups;
+  m.slot = m.pd->slot0 + m.r;
+  return m;
+}
+
+template <int P>
+__global__ __launch_bounds__(kWideWG) void k_resid_wide(Batch B, int r_id, int dot_wg, double* hist,
+                                                        int hist_stride) {
+  using T = typename RealOf<P>::T;
+  constexpr bool kNT = P != P64;  // as in k_update_r
+  __shared__ double lds[kWideWG / kWave], tiles[2][kWideWG / kWave];
+  const Slot m = wide_slot(B);
+  const int p = find_problem(B, blockIdx.x), groups = B.groups[p];
+  Scal& sc = B.scal[m.slot];
+  const int st = sc.state;
+  const double delta = sc.delta;
+  const bool writer = m.tile == 0 && threadIdx.x == 0;
+  if (st != 0) {  // uniform
+    if (st == 1 && writer) sc.state = 2;
+    return;
+  }
+  const int half = m.pd->g.half, ntiles = ceil_div(half, kMaxWG);
+  const long off = (long)m.r * half * spinor_bytes(P);
+  char* rp = reinterpret_cast<char*>(m.pd->vec[r_id]) + off;
+  const char* ap = reinterpret_cast<const char*>(m.pd->vec[V_AD]) + off;
+  // a tile's vectors are read while the tile before it (or the sum) is worked on
+  const int step = groups * kWideWG;
+  Cx<T> r[3], ad[3], r2[3], ad2[3];
+  int cb = m.tile * kWideWG + threadIdx.x;
+  if (cb < half) {
+    load_spinor<P, kNT>(rp, cb, r);
+    load_spinor<P, kNT>(ap, cb, ad);
+  }
+  const double dAd = wide_sum(partials(B, m.slot, 0), ceil_div(half, dot_wg), lds);
+  const bool ok = dAd > 0.0 && isfinite(dAd);
+  const double alpha = delta / dAd;
+  if (writer) {
+    sc.dAd = dAd;
+    if (ok) {
+      sc.alpha = alpha;
+      if (hist && sc.iter < sc.hist_len) hist[((long)m.slot * hist_stride + sc.iter) * 2] = alpha;
+    } else {
+      sc.flags |= kFlagNaN;
+      sc.state = 2;
+    }
+  }
+  if (!ok) return;  // uniform
+  const T al = (T)alpha;
+  double* part = B.partial + ((long)m.slot * kPartialSlots + 1) * B.pstride;
+  int buf = 0;
+  for (int t4 = m.tile * (kWideWG / kMaxWG); t4 < ntiles; t4 += groups * (kWideWG / kMaxWG), buf ^= 1, cb += step) {
+    double s[1] = {0.0};
+    if (cb + step < half) {
+      load_spinor<P, kNT>(rp, cb + step, r2);
+      load_spinor<P, kNT>(ap, cb + step, ad2);
+    }
+    if (cb < half) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        r[c].re = fma(-al, ad[c].re, r[c].re);
+        r[c].im = fma(-al, ad[c].im, r[c].im);
+      }
+      store_spinor<P, kNT>(rp, cb, r);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) s[0] += (double)r[c].re * r[c].re + (double)r[c].im * r[c].im;
+    }
+    // one partial per 256 sites: four waves, in order
+    wave_sum<1>(s);
+    if (threadIdx.x % kWave == 0) tiles[buf][threadIdx.x / kWave] = s[0];
+    __syncthreads();
+    if (threadIdx.x < kWideWG / kMaxWG && t4 + (int)threadIdx.x < ntiles) {
+      const double* w = &tiles[buf][threadIdx.x * (kMaxWG / kWave)];
+      double v = w[0];
+#pragma unroll
+      for (int k = 1; k < kMaxWG / kWave; ++k) v += w[k];
+      part[t4 + threadIdx.x] = v;
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      r[c] = r2[c];
+      ad[c] = ad2[c];
+    }
+  }
+}
+
+template <int P, int PX>
+__global__ __launch_bounds__(kWideWG) void k_xd_wide(Batch B, Scal* next, int x_id, int r_id, double* hist,
+                                                     int hist_stride) {
+  using T = typename RealOf<P>::T;
+  using TX = typename RealOf<PX>::T;
+  constexpr bool kNT = P != P64;  // as in k_update_xd
+  __shared__ double lds[kWideWG / kWave];
+  const Slot m = wide_slot(B);
+  const int p = find_problem(B, blockIdx.x), groups = B.groups[p];
+  const int half = m.pd->g.half;
+  const TX alpha = (TX)B.scal[m.slot].alpha;
+  char* dp = reinterpret_cast<char*>(m.pd->vec[V_D]) + (long)m.r * half * spinor_bytes(P);
+  char* xp = reinterpret_cast<char*>(m.pd->vec[x_id]) + (long)m.r * half * spinor_bytes(PX);
+  const char* rp = reinterpret_cast<const char*>(m.pd->vec[r_id]) + (long)m.r * half * spinor_bytes(P);
+  const int step = groups * kWideWG;
+  Cx<T> d[3], r[3], d2[3], r2[3];
+  Cx<TX> x[3], x2[3];
+  int cb = m.tile * kWideWG + threadIdx.x;
+  if (cb < half) {
+    load_spinor<P, kNT>(dp, cb, d);
+    load_spinor<P, kNT>(rp, cb, r);
+    load_spinor<PX, kNT>(xp, cb, x);
+  }
+  double b64;
+  const int now = beta_step(
+      B, m, next, hist, hist_stride,
+      [&] { return wide_sum(partials(B, m.slot, 1), ceil_div(half, kMaxWG), lds); }, b64);
+  if (now > 1) return;  // uniform
+  const T beta = (T)b64;
+  for (; cb < half; cb += step) {
+    if (cb + step < half) {
+      load_spinor<P, kNT>(dp, cb + step, d2);
+      load_spinor<P, kNT>(rp, cb + step, r2);
+      load_spinor<PX, kNT>(xp, cb + step, x2);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      x[c].re = fma(alpha, (TX)d[c].re, x[c].re);
+      x[c].im = fma(alpha, (TX)d[c].im, x[c].im);
+      d[c].re = fma(beta, d[c].re, r[c].re);
+      d[c].im = fma(beta, d[c].im, r[c].im);
+    }
+    store_spinor<PX, kNT>(xp, cb, x);
+    store_spinor<P, kNT>(dp, cb, d);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      d[c] = d2[c];
+      r[c] = r2[c];
+      x[c] = x2[c];
+    }
+  }
+}
+
 int blocks_of(const Batch& B) { return B.block_start[B.nprob]; }
+
+// Workgroups of a wide launch: as many as give every one of them the same number of tiles, kWideGrid at most.
+Batch wide_batch(const BatchHost& bh) {
+  Batch B = make_batch(bh, kWideWG, 1);
+  const int per = ceil_div(blocks_of(B), kWideGrid);
+  for (int p = 0; p < B.nprob; ++p) {
+    B.groups[p] = ceil_div(ceil_div(bh.probs[p].half, kWideWG), per);
+    B.block_start[p + 1] = B.block_start[p] + B.groups[p] * bh.probs[p].nrhs;
+  }
+  return B;
+}
+
 
 }  // namespace
 
-hipError_t launch_fused_resid(const BatchHost& bh, int prec, int dot_wg, double* hist, int hist_stride,
+hipError_t launch_fused_resid(const BatchHost& bh, bool wide, int prec, int dot_wg, double* hist, int hist_stride,
                               hipStream_t st) {
-  const Batch B = make_batch(bh, kMaxWG, 1);
+  const Batch B = wide ? wide_batch(bh) : make_batch(bh, kMaxWG, 1);
   const int nb = blocks_of(B);
   if (nb == 0) return hipSuccess;
+  const int r_id = prec == P64 ? V_R : V_RL;
+#define STAG_RESID(P)                                                                                  \
+  if (wide)                                                                                            \
+    k_resid_wide<P><<<nb, kWideWG, 0, st>>>(B, r_id, dot_wg, hist, hist_stride);                       \
+  else                                                                                                 \
+    k_resid<P><<<nb, kMaxWG, 0, st>>>(B, r_id, dot_wg, hist, hist_stride);                             \
+  return hipGetLastError()
   switch (prec) {
-    case P64: k_resid<P64><<<nb, kMaxWG, 0, st>>>(B, V_R, dot_wg, hist, hist_stride); break;
-    case P32: k_resid<P32><<<nb, kMaxWG, 0, st>>>(B, V_RL, dot_wg, hist, hist_stride); break;
-    case P16: k_resid<P16><<<nb, kMaxWG, 0, st>>>(B, V_RL, dot_wg, hist, hist_stride); break;
+    case P64: STAG_RESID(P64);
+    case P32: STAG_RESID(P32);
+    case P16: STAG_RESID(P16);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
+#undef STAG_RESID
 }
 
-hipError_t launch_fused_xd(const BatchHost& bh, Scal* next, int prec, int x_id, double* hist, int hist_stride,
-                           hipStream_t st) {
-  const Batch B = make_batch(bh, kMaxWG, 1);
+hipError_t launch_fused_xd(const BatchHost& bh, bool wide, Scal* next, int prec, int x_id, double* hist,
+                           int hist_stride, hipStream_t st) {
+  const Batch B = wide ? wide_batch(bh) : make_batch(bh, kMaxWG, 1);
   const int nb = blocks_of(B);
   if (nb == 0) return hipSuccess;
+  const int r_id = prec == P64 ? V_R : V_RL;
+#define STAG_XD(P, PX)                                                                                 \
+  if (wide)                                                                                            \
+    k_xd_wide<P, PX><<<nb, kWideWG, 0, st>>>(B, next, x_id, r_id, hist, hist_stride);                  \
+  else                                                                                                 \
+    k_xd<P, PX><<<nb, kMaxWG, 0, st>>>(B, next, x_id, r_id, hist, hist_stride);                        \
+  return hipGetLastError()
   switch (prec) {
-    case P64: k_xd<P64, P64><<<nb, kMaxWG, 0, st>>>(B, next, x_id, V_R, hist, hist_stride); break;
-    case P32: k_xd<P32, P32><<<nb, kMaxWG, 0, st>>>(B, next, x_id, V_RL, hist, hist_stride); break;
-    case P16: k_xd<P16, P32><<<nb, kMaxWG, 0, st>>>(B, next, x_id, V_RL, hist, hist_stride); break;
+    case P64: STAG_XD(P64, P64);
+    case P32: STAG_XD(P32, P32);
+    case P16: STAG_XD(P16, P32);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
+#undef STAG_XD
 }
 
 }  // namespace stag

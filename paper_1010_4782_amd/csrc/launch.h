@@ -91,14 +91,14 @@ hipError_t launch_copy_vec(const BatchHost& bh, int src_prec, int src_id, int ds
 hipError_t launch_add_lo_to_hi(const BatchHost& bh, int gate, int wg, hipStream_t st);  // x += x_lo ; x_lo = 0
 hipError_t launch_zero_vec(const BatchHost& bh, int prec, int v_id, int gate, int wg, hipStream_t st);
 
-// Iterations of small problems with alpha, beta and the stopping test inside the vector kernels
-// (cg_fused.hip), for at most kFusedTiles <d, Ad> partials per right-hand side.  `next`: the bank of scalars
-// that the stopping test writes (bh.d_scal is the one it reads).
+// Iterations with alpha, beta and the stopping test inside the vector kernels (cg_fused.hip): one tile of sites
+// per workgroup for at most kFusedTiles <d, Ad> partials per right-hand side, a walk over the sites otherwise
+// (wide).  `next`: the bank of scalars that the stopping test writes (bh.d_scal is the one it reads).
 constexpr int kFusedTiles = 1024;
-hipError_t launch_fused_resid(const BatchHost& bh, int prec, int dot_wg, double* hist, int hist_stride,
+hipError_t launch_fused_resid(const BatchHost& bh, bool wide, int prec, int dot_wg, double* hist, int hist_stride,
                               hipStream_t st);                     // alpha ; r -= alpha Ad ; |r|^2
-hipError_t launch_fused_xd(const BatchHost& bh, Scal* next, int prec, int x_id, double* hist, int hist_stride,
-                           hipStream_t st);                        // beta, stop test ; x += alpha d ; d = r + beta d
+hipError_t launch_fused_xd(const BatchHost& bh, bool wide, Scal* next, int prec, int x_id, double* hist,
+                           int hist_stride, hipStream_t st);       // beta, stop test ; x += alpha d ; d = r + beta d
 
 // Finalize modes (one workgroup per slot, deterministic order).
 enum Fin : int {

@@ -34,7 +34,7 @@ struct Run {
   size_t ev_used = 0;
   Scal* h_scal = nullptr;
   Scal* scal_bank[2] = {};  // the two banks of device scalars; bh.d_scal is the current one
-  bool fused = false;       // iterations run on the fused kernels (cg_fused.hip)
+  int path = 0;             // how the iterations run (iteration_path)
 };
 
 stag_status fail_arg(const std::string& m) {
@@ -109,31 +109,40 @@ hipError_t iteration(Run& R, int x_prec, int x_id, double* d_hist) {
   return e;
 }
 
-// Whether a batch's iterations run on the fused kernels (cg_fused.hip), which add the partials of a reduction
-// in every workgroup: up to kFusedTiles <d, Ad> partials per right-hand side (65536 sites of one parity in
-// 64-site workgroups), where the sums still cost less than the two launches they save (16^3x32: 46.0 us an
-// FP16 iteration against 52.8).  Sampled profiles keep the general path.
-bool fused_ok(const Run& R) {
-  if (R.profile_every > 0) return false;
-  for (const HostProb& p : R.bh.probs)
-    if (ceil_div(p.half, std::min(partial_wg(R.shape), kVecWG)) > kFusedTiles) return false;
-  return true;
+// How a batch's iterations run: on the fused kernels (cg_fused.hip), which add the partials of a reduction in
+// every workgroup, or (kGeneral) with the reductions as launches of their own.  The wide kernels hold one
+// workgroup per CU and lose to the general ones where a launch is bound by memory rather than by latency: an FP16
+// iteration of 24^3x48 takes 106.2 us against 112.8 with one right-hand side (332 thousand sites in the launch),
+// 215.7 against 217.7 with four, 468.6 against 458.0 with twelve; 32^3x64 with two (2.1 million) 401.4 against
+// 403.3.  Sampled profiles keep the general path.
+constexpr long kWideSites = 1L << 21;
+enum Path { kGeneral, kSmall, kWide };
+Path iteration_path(const Run& R) {
+  if (R.profile_every > 0) return kGeneral;
+  int most = 0;
+  long sites = 0;
+  for (const HostProb& p : R.bh.probs) {
+    most = std::max(most, ceil_div(p.half, std::min(partial_wg(R.shape), kVecWG)));
+    sites += (long)p.half * p.nrhs;
+  }
+  return most <= kFusedTiles ? kSmall : (sites <= kWideSites ? kWide : kGeneral);
 }
 
 // n CG iterations (x accumulated in precision x_prec at x_id), from and to the state between iterations.
 hipError_t iterations(Run& R, int n, int x_prec, int x_id, double* d_hist) {
   hipError_t e = hipSuccess;
   for (int i = 0; i < n && e == hipSuccess; ++i) {
-    if (!R.fused) {
+    if (R.path == kGeneral) {
       e = iteration(R, x_prec, x_id, d_hist);
       continue;
     }
     const int P = R.prec;
     e = launch_dslash(R.bh, P, EPI_PLAIN, 1, V_D, V_T, 0, 0, 1, R.shape, R.st);
     if (e == hipSuccess) e = launch_dslash(R.bh, P, EPI_XPAY_DOT, 0, V_T, V_AD, V_D, 0, 1, R.shape, R.st);
-    if (e == hipSuccess) e = launch_fused_resid(R.bh, P, partial_wg(R.shape), d_hist, R.hist_len, R.st);
+    if (e == hipSuccess) e = launch_fused_resid(R.bh, R.path == kWide, P, partial_wg(R.shape), d_hist, R.hist_len,
+                                                 R.st);
     Scal* next = R.bh.d_scal == R.scal_bank[0] ? R.scal_bank[1] : R.scal_bank[0];
-    if (e == hipSuccess) e = launch_fused_xd(R.bh, next, P, x_id, d_hist, R.hist_len, R.st);
+    if (e == hipSuccess) e = launch_fused_xd(R.bh, R.path == kWide, next, P, x_id, d_hist, R.hist_len, R.st);
     R.bh.d_scal = next;
   }
   return e;
@@ -462,7 +471,7 @@ stag_status solve_batch(int nprob, const stag_problem* probs, const stag_cg_para
     if (prm.autotune && mixed && !has_shape(key64))
       STAG_HIP_TRY(tune_batch(R.bh, key64, P64, st, nullptr, nullptr, V_X, V_TMPO));
     R.shape64 = lookup_shape(R.bh, key64, P64);
-    R.fused = fused_ok(R);
+    R.path = iteration_path(R);
   }
 
   // ---- scalars ----

@@ -69,3 +69,26 @@ def test_fused_batch_of_lattices(gpu_lib):
         out.append((xs, [(i["iters"], i["n_reliable"], i["true_resid"]) for i in info]))
     assert all(torch.equal(a, b) for a, b in zip(out[0][0], out[1][0]))
     assert out[0][1] == out[1][1]
+
+
+# 2048 and 1064 partials of <d, Ad>, more than the one-tile kernels take: even, and ragged tiles with a slot that
+# never runs; slots stop at different iterations
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
+@pytest.mark.parametrize("dims,nrhs", [((16, 16, 16, 64), 1), ((18, 10, 14, 54), 3)])
+def test_wide_iterations_are_the_general_ones(gpu_lib, dims, nrhs, prec):
+    test_fused_iterations_are_the_general_ones(gpu_lib, dims, nrhs, prec)
+
+
+def test_wide_batch_of_lattices(gpu_lib):
+    from paper_1010_4782_amd.stagcg import cg_solve_batch
+
+    print("wide CG batch", flush=True)
+    shapes = [((2, 4, 4, 2), 2), ((16, 16, 16, 40), 2), ((6, 10, 4, 6), 3)]  # one of them a single tile
+    lats = [setup(d, 105 + i) for i, (d, _) in enumerate(shapes)]
+    bs = [torch.from_numpy(gaussian_source(d, 110 + i, n)).cuda() for i, (d, n) in enumerate(shapes)]
+    out = []
+    for profile in (0, 1000):
+        xs, info = cg_solve_batch([(l, b, 0.2, None) for l, b in zip(lats, bs)], prec="f16", profile=profile)
+        out.append((xs, [(i["iters"], i["n_reliable"], i["true_resid"]) for i in info]))
+    assert all(torch.equal(a, b) for a, b in zip(out[0][0], out[1][0]))
+    assert out[0][1] == out[1][1]
