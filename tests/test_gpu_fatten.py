@@ -38,7 +38,7 @@ def test_fatten_links_match_oracle(gpu_lib, dims, u0):
 @pytest.mark.parametrize("dims", [(6, 2, 10, 4), (2, 6, 18, 2), (10, 6, 8, 6)])
 def test_fatten_links_uneven_z_blocks(gpu_lib, dims):
     """z extents that the eight per-XCD blocks of planes divide unevenly, and volumes that are no multiple
-    of a workgroup's 256 sites."""
+    of a workgroup's sites."""
     print(f"fatten dims={dims}", flush=True)
     U = random_su3_field(dims, 77)
     _, fat, lng = _fatten(dims, torch.from_numpy(U).cuda(), 0.9)
