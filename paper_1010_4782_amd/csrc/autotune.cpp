@@ -38,6 +38,14 @@ int rhs_divisor(const BatchHost& bh) {
   return r;
 }
 
+// The most right-hand sides per lane that any problem of the batch can use: a lane with fewer left masks the rest.
+int rhs_most(const BatchHost& bh) {
+  int n = 1, r = 1;
+  for (const auto& p : bh.probs) n = std::max(n, p.nrhs);
+  while (r < 8 && r < n) r <<= 1;
+  return r;
+}
+
 // The colour vectors of one time slice, all right-hand sides, of the largest lattice.
 double slice_bytes(const BatchHost& bh, int prec) {
   double m = 0.0;
@@ -52,6 +60,13 @@ double slice_bytes(const BatchHost& bh, int prec) {
 //    parity on, where reading each link once is worth the one wave per SIMD it leaves (28^3x96 x 8: FP64 778 us
 //    against 929 at 4, FP32 376 and 444; 24^3x48: 259 and 261, 129 and 134; at 16^3x32 4 is faster, 45 us).
 //  * Fewer while that leaves less than two waves per SIMD (16^3x32 x 4: FP64 30 us at 2 per lane, 33 at 4).
+//  * Counts that are no multiple of 4 or 8 mask lanes of the last group instead of taking one or two per lane, where
+//    that leaves at most two thirds of the groups: links are read, and x, y neighbours found in L1, once per
+//    group.  28^3x96: 3 RHS FP64 739 -> 500 us, FP32 405 -> 313, FP16 247 -> 190; 5 RHS 982 -> 582, 609 -> 394,
+//    378 -> 306; 7 RHS 1283 -> 728; 9 RHS 1582 -> 960.  8 per lane only if the last lane has 5 or more (9 RHS:
+//    1072 us at 8 per lane, 960 at 4; 12: 1168 and 1105).  Enough waves must remain to hide the longer lane:
+//    2048 in FP64 (16^3x32 x 5: 51 -> 43 us), 5120 in FP32 (20^3x40 x 3, 2500 waves: 57 us masked, 50 not), 7168
+//    in FP16 (24^3x48 x 3, 5184 waves: 70 and 64), where 2 per lane gains nothing (64 -> 62..67).
 //  * Tile order: on a small lattice the lattice order, whose t neighbours are in an XCD's 4 MiB L2 anyway
 //    (16^3x32 x 8, FP64: 45 us, the z-block order 51).  From 2 MiB of colour vectors per time slice the orders
 //    that sweep t through one XCD's share: z blocks where the lattice allows them (32^3x64 x 8: FP64 781 us
@@ -63,13 +78,23 @@ DslashShape heuristic(const BatchHost& bh, int prec) {
   const bool r8_f16 = prec == P16 && !bh.long12, large = bh.max_half >= kLargeHalf;
   const bool sweep = slice_bytes(bh, prec) >= 2.0 * 1024 * 1024;
   DslashShape s;
-  s.r = std::min(rhs_divisor(bh), r8_f16 || (prec != P16 && large) ? 8 : 4);
+  const int most = r8_f16 || (prec != P16 && large) ? 8 : 4;
+  s.r = std::min(rhs_divisor(bh), most);
   auto waves = [&](int r) {
     long n = 0;
-    for (const auto& p : bh.probs) n += (long)ceil_div(p.half, kWave) * (p.nrhs / r);
+    for (const auto& p : bh.probs) n += (long)ceil_div(p.half, kWave) * ceil_div(p.nrhs, r);
     return n;
   };
+  auto mostly_idle = [&](int r) {  // a last lane with half of its right-hand sides or more masked
+    return std::any_of(bh.probs.begin(), bh.probs.end(), [&](const HostProb& p) { return (r - p.nrhs % r) % r >= r / 2; });
+  };
   while (s.r > 1 && waves(s.r) < 2048) s.r >>= 1;
+  const long enough = prec == P64 ? 2048 : (prec == P32 ? 5120 : 7168);
+  for (int r = std::min(rhs_most(bh), most); r > s.r && r >= (prec == P16 ? 4 : 2); r >>= 1)
+    if (waves(r) >= enough && 3 * waves(r) <= 2 * waves(s.r) && !(r == 8 && mostly_idle(r))) {
+      s.r = r;
+      break;
+    }
   s.wg = prec == P16 && s.r == 8 ? 128 : 64;
   s.order = sweep || (prec != P16 && large) ? 1 : 0;
   if (s.order && !dslash_shape_valid(bh, prec, s)) s.order = 0;
@@ -89,7 +114,7 @@ DslashShape lookup_shape(const BatchHost& bh, const std::string& key, int prec) 
   auto it = g_table.find(key);
   if (it != g_table.end()) {
     DslashShape s = it->second;
-    s.r = std::min(s.r, rhs_divisor(bh));
+    s.r = std::min(s.r, rhs_most(bh));
     if (!dslash_shape_valid(bh, prec, s)) {  // a loaded entry that does not fit this batch
       s.lds = s.order = 0;
       s.chunks = 1;
@@ -112,7 +137,9 @@ bool has_shape(const std::string& key) {
   return g_table.count(key) != 0;
 }
 
-// Time every candidate shape on the batch's Dslash (in_id -> out_id, output parity 1, plain epilogue).
+// Time every candidate shape on the batch's Dslash (in_id -> out_id, output parity 1, plain epilogue).  Where the
+// untuned default masks lanes it is timed too and kept if it is the fastest; best_out and all hold shapes that
+// divide the right-hand sides, the ones stag_set_dslash_shape takes.
 hipError_t tune_batch(const BatchHost& bh, const std::string& key, int prec, hipStream_t st, DslashShape* best_out,
                       std::vector<std::pair<DslashShape, float>>* all, int in_id, int out_id) {
   const int rmax = rhs_divisor(bh);
@@ -137,13 +164,19 @@ hipError_t tune_batch(const BatchHost& bh, const std::string& key, int prec, hip
       for (int c : {2, 3, 4, 6}) cands.push_back(DslashShape{wg, r, 0, 1, c});
   for (int r : {8, 4})
     for (int chunks : {1, 2, 4}) cands.push_back(DslashShape{64, r, 0, 2, chunks});
-  for (const DslashShape& sh : cands) {
+  const size_t dividing = cands.size();
+  const DslashShape untuned = heuristic(bh, prec);
+  if (untuned.r > rmax) cands.push_back(untuned);
+  DslashShape keep{};
+  float keep_us = 1e30f;
+  for (size_t i = 0; i < cands.size(); ++i) {
+    const DslashShape& sh = cands[i];
     if (e != hipSuccess) break;
     if (!dslash_shape_valid(bh, prec, sh)) continue;
     for (int w = 0; w < 2 && e == hipSuccess; ++w)
       e = launch_dslash(bh, prec, EPI_PLAIN, 1, in_id, out_id, 0, 0, 3, sh, st);
     if (e == hipSuccess) e = hipEventRecord(e0, st);
-    for (int i = 0; i < reps && e == hipSuccess; ++i)
+    for (int k = 0; k < reps && e == hipSuccess; ++k)
       e = launch_dslash(bh, prec, EPI_PLAIN, 1, in_id, out_id, 0, 0, 3, sh, st);
     if (e == hipSuccess) e = hipEventRecord(e1, st);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -151,6 +184,11 @@ hipError_t tune_batch(const BatchHost& bh, const std::string& key, int prec, hip
     if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
     if (e != hipSuccess) break;
     const float us = 1e3f * ms / reps;
+    if (us < keep_us) {
+      keep_us = us;
+      keep = sh;
+    }
+    if (i >= dividing) continue;
     if (all) all->push_back({sh, us});
     if (us < best_us) {
       best_us = us;
@@ -160,7 +198,7 @@ hipError_t tune_batch(const BatchHost& bh, const std::string& key, int prec, hip
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (e == hipSuccess) {
-    pin_shape(key, best);
+    pin_shape(key, keep);
     if (best_out) *best_out = best;
   }
   return e;

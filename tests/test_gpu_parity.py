@@ -6,7 +6,8 @@ import torch
 from oracle import lowprec
 from oracle.cg import cg, true_residual
 from oracle.dslash import apply_m, dslash_at_sites, dslash_eo
-from stag_inputs import fat_field, gaussian_source, random_su3_field
+from stag_inputs import (fat_field, fat_field_device, gaussian_source, gaussian_source_device, random_su3_field,
+                         random_su3_field_device)
 
 pytestmark = pytest.mark.gpu
 
@@ -735,3 +736,29 @@ def test_operator_calls_are_their_single_rhs_calls(gpu_lib, dims, nrhs, su3):
         ref = lat.slice_norm2(v, 3, 4 * 0.07**2)
         lat.slice_norm2(lat.dslash(v, 1), 3, 1.0, out=ref, accumulate=True)
         assert torch.max(torch.abs(c - ref) / ref) <= 2 * 3 * 6 * dims[0] * dims[1] * dims[2] * 2.0**-53
+
+
+# right-hand sides masked in the last lane: 4 per lane (FP64 alone; every precision) and 8 per lane (FP64; FP64,
+# FP32 and, with 18-real three-hop links, FP16)
+@pytest.mark.parametrize("dims,nrhs,most", [((20, 20, 20, 40), 3, 4), ((22, 18, 26, 30), 9, 4), ((16, 16, 32, 64), 5, 8),
+                                            ((24, 24, 32, 50), 7, 8)])
+@pytest.mark.parametrize("su3", [False, True])
+def test_masked_right_hand_sides_are_single_ones(gpu_lib, dims, nrhs, most, su3):
+    from paper_1010_4782_amd.stagcg import Lattice
+
+    print(f"masked right-hand sides {dims} x {nrhs} su3 {su3}", flush=True)
+    lat = Lattice(dims)
+    lat.load_links(fat_field_device(dims, 67), random_su3_field_device(dims, 68), NAIK, precs=("f64", "f32", "f16"),
+                   long_su3=su3)
+    v = gaussian_source_device(dims, 69, nrhs)
+    for prec in ("f64", "f32", "f16"):
+        for par in (0, 1):
+            out = lat.dslash(v, par, prec=prec)
+            for r in range(nrhs):
+                assert torch.equal(out[r], lat.dslash(v[r:r + 1].contiguous(), par, prec=prec)[0]), (prec, par, r)
+    mass = [0.3 + 0.1 * r for r in range(nrhs)]
+    x, info = lat.cg_solve(v, mass)
+    assert info[0]["dslash_rhs"] == most
+    for r in (0, nrhs - 1):
+        y, one = lat.cg_solve(v[r:r + 1].contiguous(), mass[r])
+        assert torch.equal(x[r], y[0]) and info[r]["iters"] == one[0]["iters"], r
