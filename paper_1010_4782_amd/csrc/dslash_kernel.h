@@ -382,11 +382,15 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
     return;
   }
 
+  // One right-hand side in FP64 with 18-real three-hop links stores piecewise: 22x28x26x50 162 us against 168
+  // staged (28^3x96 425 and 433).  With 12-real links (137 us staged, 142 piecewise) and in FP32 (101 and 103)
+  // staging is faster there too.
+  constexpr bool kStaged = !LDS && !(P == P64 && R == 1 && !C12);
   char* out = vec(out_id) + (long)r0 * rstride;
   if (EPI == EPI_PLAIN) {
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      if (on[r]) store_out<P, !LDS>(out + r * rstride, cb_raw, live, g.half, acc[r]);
+      if (on[r]) store_out<P, kStaged>(out + r * rstride, cb_raw, live, g.half, acc[r]);
     return;
   }
 
@@ -409,7 +413,7 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
 #pragma unroll
       for (int c = 0; c < 3; ++c) o[c] = Cx<T>{a * xv[c].re - acc[r][c].re, a * xv[c].im - acc[r][c].im};
     }
-    store_out<P, !LDS>(out + r * rstride, cb_raw, live, g.half, o);
+    store_out<P, kStaged>(out + r * rstride, cb_raw, live, g.half, o);
     if (live) {
       if (EPI == EPI_XPAY_DOT) {
 #pragma unroll
