@@ -89,12 +89,24 @@ __device__ __forceinline__ NetView net_view(const NetLaunch& l, bool second) {
                  l.a[0].w,
                  second ? l.gy[1] : l.gy[0]};
 }
+constexpr int kNetVecWG = kWave;  // k_net_layer
+
 // A layer launch: workgroups in XCD-sweep order (xcd_sweep_site), the two parities of a tile next to each
 // other, so that the activations which both sides and the neighbouring sites read are shared in an XCD's L2.
 __device__ __forceinline__ NetView net_side(const NetLaunch& l, int& cb) {
   const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
   const Geo& g = l.a[0].g;
   cb = xcd_sweep_site(xcd, (l.n == 2 ? j >> 1 : j) * blockDim.x + threadIdx.x, g.stride[3], g.L[3]);
+  return net_view(l, l.n == 2 && (j & 1));
+}
+
+// The same with one contiguous range of whole 64-site link blocks per XCD, net_range_len sites.
+__host__ __device__ inline int net_range_len(int half) { return ceil_div(half, 8 * kWave) * kWave; }
+__device__ __forceinline__ NetView net_range_side(const NetLaunch& l, int& cb) {
+  const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+  const int half = l.a[0].g.half, n = net_range_len(half);
+  const int i = (l.n == 2 ? j >> 1 : j) * blockDim.x + threadIdx.x;
+  cb = i < n && xcd * n + i < half ? xcd * n + i : -1;
   return net_view(l, l.n == 2 && (j & 1));
 }
 
@@ -123,10 +135,17 @@ __device__ __forceinline__ void transported(const NetView& a, const Site& s, lon
   }
 }
 
+// Layers with one channel on a side.  Large lattices are bound by the reads of the links (24^3x48: 382 MB of
+// 510, 8 -> 1 in 80 us, 1 -> 8 in 76), small ones by the chain of load latencies: the next direction's link and
+// channels are in flight while a direction is transported and mixed, in single-wave workgroups, so that a small
+// lattice spreads over more CUs.  Without that 8 -> 1 took 96 us, and a whole network call with 1, 8, 8 and 1
+// channels at 8^4 45 us instead of 39, with 1, 4 and 1 at 10x8x8x14 28 instead of 19.  XCD ranges of whole link
+// blocks: a wave whose sites straddle two blocks reads twice the cache lines of a link (26x26x20x30, 1, 4 and 1
+// channels: 92 us in the sweep, 87 in ranges).
 template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_net_layer(NetLaunch l) {
+__global__ __launch_bounds__(kNetVecWG) void k_net_layer(NetLaunch l) {
   int cb;
-  const NetView a = net_side(l, cb);
+  const NetView a = net_range_side(l, cb);
   if (cb < 0) return;
   const Site s = site_of(cb, a.out_par, a.g);
   const long blk = cb >> 6;
@@ -150,19 +169,40 @@ __global__ __launch_bounds__(256) void k_net_layer(NetLaunch l) {
     }
   }
   if (a.in_other) {
-#pragma unroll 1
+    Cx<float> u[2][9], v[2][CIN][3];
+    auto fetch = [&](int d) {
+      const int mu = (d - 1) & 3;
+      const bool fwd = d <= 4;
+      if (a.g.long12)
+        load_link<P32, true>(a.links, blk, 4 * mu + (fwd ? 0 : 1), lane, 1.f, u[d & 1]);
+      else
+        load_link<P32, false>(a.links, blk, 4 * mu + (fwd ? 0 : 1), lane, 1.f, u[d & 1]);
+      load_channels<CIN, CIN>(a.in_other, a.g.half, neighbour(s, a.g, mu, a.g.h1[mu], fwd), 0, v[d & 1]);
+      asm volatile("" ::: "memory");  // these loads stay ahead of the products, and the products of the next fetch
+    };
+    fetch(1);
+#pragma unroll
     for (int d = 1; d <= 8; ++d) {
-      Cx<float> t[CIN][3];
-      transported<CIN>(a, s, blk, lane, d, t);
+      if (d < 8) fetch(d + 1);
+      Cx<float> w9[9];
+#pragma unroll
+      for (int e = 0; e < 9; ++e) {
+        const Cx<float> w = u[d & 1][e];
+        w9[e] = d <= 4 ? w : Cx<float>{-w.re, -w.im};
+      }
       const float2* wd = a.w + d * COUT * CIN;
 #pragma unroll
-      for (int ci = 0; ci < CIN; ++ci)
+      for (int ci = 0; ci < CIN; ++ci) {
+        Cx<float> t[3] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+        matvec_acc(w9, v[d & 1][ci], t);
 #pragma unroll
         for (int c = 0; c < COUT; ++c) {
           const float2 w = wd[c * CIN + ci];
 #pragma unroll
-          for (int i = 0; i < 3; ++i) cmac_f(acc[c][i], w, t[ci][i]);
+          for (int i = 0; i < 3; ++i) cmac_f(acc[c][i], w, t[i]);
         }
+      }
+      asm volatile("" ::: "memory");
     }
   }
   store_channels<COUT>(a.out, a.g.half, cb, acc);
@@ -587,16 +627,20 @@ __global__ __launch_bounds__(256) void k_sum_partials(const double* partial, int
 hipError_t launch_net_layer(const NetLaunch& l, int cin, int cout, hipStream_t st) {
   if (l.n == 0) return hipSuccess;
   const Geo& g = l.a[0].g;
-  const int nb = 8 * l.n * (int)((xcd_sweep_len(g.stride[3], g.L[3]) + 255) / 256);
+  const long len = xcd_sweep_len(g.stride[3], g.L[3]);
+  // The matrix-core layer too takes single-wave workgroups below two waves per SIMD (a network of 1, 8, 8 and 1
+  // channels at 12^3x16: 47 us against 54); at 16^3x32, just there, four waves are faster: 84 us against 93.
+  const int wg = 8 * l.n * len < 2048L * kWave ? kWave : 256;
+  const int nv = 8 * l.n * (net_range_len(g.half) / kNetVecWG), nb = 8 * l.n * (int)((len + wg - 1) / wg);
   // layers with at least two channels on both sides mix on the matrix cores; 1 -> C and C -> 1
   // would fill at most a quarter of an MFMA tile and stay on the vector units
 #define STAG_NET_LAYER(I, O) \
-  if (cin == I && cout == O) { k_net_layer<I, O><<<nb, 256, 0, st>>>(l); return hipGetLastError(); }
+  if (cin == I && cout == O) { k_net_layer<I, O><<<nv, kNetVecWG, 0, st>>>(l); return hipGetLastError(); }
 #define STAG_NET_LAYER_MFMA(I, O) \
   if (cin == I && cout == O) { \
     for (int i = 0; i < l.n; ++i) \
       if (!l.a[i].in_same || !l.a[i].in_other) return hipErrorInvalidValue;  /* inner layers: both parities set */ \
-    k_net_layer_mfma<I, O><<<nb, 256, 0, st>>>(l); return hipGetLastError(); }
+    k_net_layer_mfma<I, O><<<nb, wg, 0, st>>>(l); return hipGetLastError(); }
   STAG_NET_LAYER(1, 1) STAG_NET_LAYER(1, 2) STAG_NET_LAYER(2, 1) STAG_NET_LAYER_MFMA(2, 2)
   STAG_NET_LAYER(1, 4) STAG_NET_LAYER(4, 1) STAG_NET_LAYER_MFMA(4, 4)
   STAG_NET_LAYER(1, 8) STAG_NET_LAYER(8, 1) STAG_NET_LAYER_MFMA(8, 8)

@@ -95,7 +95,7 @@ def test_net_loss_and_gradients_match_oracle(gpu_lib, dims, width):
         assert rel(g, gr) <= 1e-4
 
 
-@pytest.mark.parametrize("dims,width", [((2, 6, 6, 4), 8), ((6, 2, 2, 10), 2), ((10, 14, 18, 26), 4)])
+@pytest.mark.parametrize("dims,width", [((2, 6, 6, 4), 8), ((6, 2, 2, 10), 2), ((10, 14, 18, 26), 4), ((14, 18, 22, 26), 2)])
 def test_net_uneven_ranges_match_oracle(gpu_lib, dims, width):
     """Time slices that the eight XCD ranges divide unevenly (36, 12 and 1260 sites per parity), a ragged last
     wave, and (10x14x18x26, 512 chunks of 64 sites) gradient waves with a second chunk: forward within
