@@ -57,9 +57,9 @@ double slice_bytes(const BatchHost& bh, int prec) {
 // Without a tuned entry.  64-site workgroups (128 for FP16 at 8 RHS per lane); every choice gives the same bits.
 //  * Right-hand sides per lane: up to 4, where a lane's registers still leave two or three waves per SIMD; 8 for
 //    FP16 with 18-real three-hop links (no third-row rebuild), and for FP32 and FP64 from 2^18 sites of one
-//    parity on, where reading each link once is worth the one wave per SIMD it leaves (28^3x96 x 8: FP64 778 us
-//    against 929 at 4, FP32 376 and 444; 24^3x48: 259 and 261, 129 and 134; at 16^3x32 4 is faster, 45 us).
-//  * Fewer while that leaves less than two waves per SIMD (16^3x32 x 4: FP64 30 us at 2 per lane, 33 at 4).
+//    parity on, where reading each link once is worth the one wave per SIMD it leaves (28^3x96 x 8: FP64 803 us
+//    against 994 at 4, FP32 534 and 616; 24^3x48: 276 and 280, 178 and 187; at 16^3x32 4 is faster, 48 and 57).
+//  * Fewer while that leaves less than two waves per SIMD (16^3x32 x 4: FP64 34 us at 2 per lane, 37 at 4).
 //  * Counts that are no multiple of 4 or 8 mask lanes of the last group instead of taking one or two per lane, where
 //    that leaves at most two thirds of the groups: links are read, and x, y neighbours found in L1, once per
 //    group.  28^3x96: 3 RHS FP64 739 -> 500 us, FP32 405 -> 313, FP16 247 -> 190; 5 RHS 982 -> 582, 609 -> 394,

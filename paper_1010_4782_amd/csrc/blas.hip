@@ -584,7 +584,7 @@ constexpr int kSliceWG = 1024;
 __global__ __launch_bounds__(kSliceWG) void k_slice_norm2(const char* v, const double* n2, long half, int slice,
                                                           int lt, int group, double weight, int accumulate,
                                                           double* out) {
-  __shared__ double lds[2 * (kSliceWG / kWave)];
+  __shared__ double lds[2][kSliceWG / kWave];
   const int t = blockIdx.x % lt, g = blockIdx.x / lt;
   double acc[2] = {0.0, 0.0};
   const long words = 3L * slice;
@@ -608,8 +608,17 @@ __global__ __launch_bounds__(kSliceWG) void k_slice_norm2(const char* v, const d
       for (int k = threadIdx.x; k < slice; k += kSliceWG) acc[1] += q[k];
     }
   }
-  block_sum<2, kSliceWG / kWave>(acc, lds);
-  if (threadIdx.x == 0) {
+  // the waves' sums are added in pairs: one after the other, 15 roundings near the size of the result took the
+  // correlator of 28^3x96 from 1.2e-16 to 1.6e-16 off
+  wave_sum<2>(acc);
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  if (lane == 0)
+    for (int k = 0; k < 2; ++k) lds[k][wave] = acc[k];
+  __syncthreads();
+  if (wave != 0) return;
+  for (int k = 0; k < 2; ++k) acc[k] = lane < kSliceWG / kWave ? lds[k][lane] : 0.0;
+  wave_sum<2>(acc);
+  if (lane == 0) {
     const double val = weight * acc[0] + acc[1];
     out[blockIdx.x] = accumulate ? out[blockIdx.x] + val : val;
   }
