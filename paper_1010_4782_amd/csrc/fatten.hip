@@ -32,9 +32,9 @@
 // touches 64 cache lines for a sixth of their bytes.  What is written is not read again by the same launch: it
 // goes past L2 (2% of the whole).  Workgroups are single waves: nothing is shared between waves, the last round of
 // a launch drains a wave at a time, and a 16^3x32 field still fills the chip (0.59 ms against 0.71).
-// Sums of staples are formed without the larger term c1 U, which is added last: against extended precision the
-// one-hop links of an 8^4 field are off by 1.2e-16 (relative, root mean square), 1.6e-16 when every wrap was
-// rounded to memory.
+// The sum of each nu starts from zero and the larger term c1 U comes last: against extended precision the one-hop
+// links of an 8^4 field are off by 0.9e-16 (relative, root mean square), 1.2e-16 as one running sum and 1.6e-16
+// when every wrap was rounded to memory.
 // Both link fields of a 24^3x48 field take 2.9 ms; 110 launches over matrices in the user layout, one wrap each,
 // took 16.6 ms.
 #include <hip/hip_runtime.h>
@@ -143,20 +143,19 @@ __device__ __forceinline__ void issue_all() { asm volatile("" ::: "memory"); }
 // A B; an element is the sum of three complex products, each rounded by itself: against extended precision the
 // long links are off by 0.95e-16 that way, 1.1e-16 as one chain of six fused products
 __device__ __forceinline__ M3 mul(const M3& a, const M3& b) {
-  M3 c;
+  M3 c = zero();
 #pragma unroll
-  for (int i = 0; i < 3; ++i)
+  for (int i = 0; i < 3; ++i) {
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      double2 s = {0.0, 0.0};
+    for (int k = 0; k < 3; ++k)
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
+      for (int j = 0; j < 3; ++j) {
         const double2 x = a.e[3 * i + k], y = b.e[3 * k + j];
-        s.x += x.x * y.x - x.y * y.y;
-        s.y += x.x * y.y + x.y * y.x;
+        c.e[3 * i + j].x += x.x * y.x - x.y * y.y;
+        c.e[3 * i + j].y += x.x * y.y + x.y * y.x;
       }
-      c.e[3 * i + j] = s;
-    }
+    __builtin_amdgcn_sched_barrier(0);  // row by row: interleaved, they cost k_long its third wave per SIMD
+  }
   return c;
 }
 
@@ -327,7 +326,7 @@ __global__ __launch_bounds__(kFatWG, 1) void k_outer(const double2* __restrict__
   const long f9 = 9L * g.vol;
   const double2* Um = U + MU * f9;
   const int mu1 = hop(c, g, MU, 1);
-  M3 h, m[2][3], acc = zero();
+  M3 h, m[2][3], part, acc = zero();
   auto fetch = [&](int i, M3(&w)[3]) {
     if (i == 12) {
       w[0] = ld(Um, g, n);
@@ -351,6 +350,7 @@ __global__ __launch_bounds__(kFatWG, 1) void k_outer(const double2* __restrict__
     const bool plus = ((i >> 1) & 1) == 0;
     const M3(&w)[3] = m[i & 1];
     if ((i & 1) == 0) {
+      if ((i & 3) == 0) part = zero();
       h = zero();
       if (plus)
         wrap_acc<true>(h, w[0], w[1], w[2]);
@@ -360,13 +360,19 @@ __global__ __launch_bounds__(kFatWG, 1) void k_outer(const double2* __restrict__
 #pragma unroll
       for (int e = 0; e < 9; ++e) h.e[e] = double2{fma(cl, h.e[e].x, w[1].e[e].x), fma(cl, h.e[e].y, w[1].e[e].y)};
       if (plus)
-        wrap_acc<true>(acc, w[0], h, w[2]);
+        wrap_acc<true>(part, w[0], h, w[2]);
       else
-        wrap_acc<false>(acc, w[0], h, w[2]);
+        wrap_acc<false>(part, w[0], h, w[2]);
+      if ((i & 3) == 3)
+#pragma unroll
+        for (int e = 0; e < 9; ++e) {
+          acc.e[e].x += part.e[e].x;
+          acc.e[e].y += part.e[e].y;
+        }
     }
     issue_all();
   }
-  // c1 U_mu, the largest term, last: the 36 roundings of the sum are then relative to the staples alone
+  // c1 U_mu, the largest term, last: the sum's roundings are then relative to the staples alone
 #pragma unroll
   for (int e = 0; e < 9; ++e) {
     const double2 u = m[0][0].e[e];
