@@ -88,12 +88,9 @@ __device__ __forceinline__ int beta_step(const Batch& B, const Slot& m, Scal* ne
     }
   }
   if (m.tile == 0 && threadIdx.x == 0) {
-    // every word of the slot, then the ones that changed
-    constexpr int kWords = sizeof(Scal) / 8;
-    const double* from = reinterpret_cast<const double*>(&pre);
-    double* to = reinterpret_cast<double*>(next + m.slot);
-#pragma unroll
-    for (int i = 0; i < kWords; ++i) to[i] = from[i];
+    // the whole slot, as bytes (a copy through another type need not be ordered with the members' stores), then
+    // the members that changed
+    __builtin_memcpy(next + m.slot, &pre, sizeof(Scal));
     if (st == 0) {
       Scal& sc = next[m.slot];
       sc.state = now;
