@@ -212,15 +212,15 @@ bool save_table(const char* path) {
   size_t i = 0;
   for (const auto& kv : g_table) {
     f << "  \"" << kv.first << "\": [" << kv.second.wg << ", " << kv.second.r << ", " << kv.second.lds << ", "
-      << kv.second.order << ", " << kv.second.chunks << "]"
+      << kv.second.order << ", " << kv.second.chunks << (kv.second.sweep ? ", 1]" : "]")
       << (++i < g_table.size() ? ",\n" : "\n");
   }
   f << "}\n";
   return (bool)f;
 }
 
-// Reads the format save_table writes: one "key": [wg, r, lds, order, chunks] entry per line (lds and
-// order may be absent: 0; chunks: 1).
+// Reads the format save_table writes: one "key": [wg, r, lds, order, chunks, sweep] entry per line (lds, order and
+// sweep may be absent: 0; chunks: 1).
 bool load_table(const char* path, int* n_loaded) {
   std::ifstream f(path);
   if (!f) return false;
@@ -233,13 +233,14 @@ bool load_table(const char* path, int* n_loaded) {
     const size_t q1 = line.find('"', q0 + 1);
     const size_t b0 = line.find('[', q1);
     if (q1 == std::string::npos || b0 == std::string::npos) return false;
-    int wg = 0, r = 0, lds = 0, order = 0, chunks = 1;
-    const int got = std::sscanf(line.c_str() + b0, "[%d , %d , %d , %d , %d]", &wg, &r, &lds, &order, &chunks);
+    int wg = 0, r = 0, lds = 0, order = 0, chunks = 1, sweep = 0;
+    const int got =
+        std::sscanf(line.c_str() + b0, "[%d , %d , %d , %d , %d , %d]", &wg, &r, &lds, &order, &chunks, &sweep);
     if (got < 2) return false;
     if ((wg != 64 && wg != 128 && wg != 256) || (r != 1 && r != 2 && r != 4 && r != 8) || (lds != 0 && lds != 1) ||
-        (order < 0 || order > 2) || chunks < 1 || chunks > 64)
+        (order < 0 || order > 2) || chunks < 1 || chunks > 64 || (sweep != 0 && sweep != 1) || (sweep && (lds || order)))
       return false;
-    tmp[line.substr(q0 + 1, q1 - q0 - 1)] = DslashShape{wg, r, lds, order, chunks};
+    tmp[line.substr(q0 + 1, q1 - q0 - 1)] = DslashShape{wg, r, lds, order, chunks, sweep != 0};
     ++n;
   }
   std::lock_guard<std::mutex> lk(g_mu);

@@ -139,6 +139,24 @@ def test_tune_cache_roundtrip(lib, tmp_path):
     assert lib.stag_tune_cache_load(None) == 1
 
 
+def test_tune_cache_keeps_the_sweep(lib, tmp_path):
+    """A lattice-order entry that the XCDs sweep in t keeps that through a round trip; a file without the field
+    reads as no sweep, and the sweep goes with the lattice order and without LDS staging only."""
+    src, out = tmp_path / "tune.json", tmp_path / "out.json"
+    src.write_text('{\n  "p0:6x10x14x2/9": [64, 4, 0, 0, 1, 1],\n  "p0:6x10x14x2/8": [64, 8, 0, 0, 1, 0],\n'
+                   '  "p0:6x10x14x2/7": [64, 8, 0, 0, 1]\n}\n')
+    for path in (src, out):  # the second pass reads what the first one wrote
+        assert lib.stag_tune_cache_load(str(path).encode()) == 0
+        assert lib.stag_tune_cache_save(str(out).encode()) == 0
+        text = out.read_text()
+        assert '"p0:6x10x14x2/9": [64, 4, 0, 0, 1, 1]' in text
+        assert '"p0:6x10x14x2/8": [64, 8, 0, 0, 1]' in text and '"p0:6x10x14x2/7": [64, 8, 0, 0, 1]' in text
+    bad = tmp_path / "bad.json"
+    for entry in ("[64, 4, 0, 0, 1, 2]", "[64, 4, 0, 1, 1, 1]", "[64, 4, 1, 0, 1, 1]", "[64, 8, 0, 2, 1, 1]"):
+        bad.write_text('{\n  "p0:6x10x14x2/8": %s\n}\n' % entry)
+        assert lib.stag_tune_cache_load(str(bad).encode()) == 1, entry
+
+
 def test_shape_arguments_validated(lib):
     assert lib.stag_set_dslash_shape(None, 0, 1, None) == 1
     assert lib.stag_tune_dslash(None, 0, 1, None, None, 0, None, None) == 1
