@@ -281,8 +281,9 @@ stag_status stag_cg_solve_batch(int32_t nprob, const stag_problem* probs, const 
  * precision `prec` on this lattice (on library-owned scratch vectors, on `stream`), keeps the fastest
  * for later stag_dslash / stag_cg_solve calls with the same key, and returns it in *best; if all is
  * non-NULL, up to max_all timed candidates are written there and their count to *n_all.
- * Where nrhs is no multiple of the lanes' count, the untuned default (which then masks right-hand sides
- * of the last lane) is timed too and kept if it is the fastest; *best and all stay shapes that divide nrhs.
+ * The untuned default may be a shape that stag_set_dslash_shape does not take: one that masks right-hand
+ * sides of the last lane (nrhs no multiple of rhs_per_lane), or the lattice order swept in t per XCD.  It is
+ * then timed too and kept if it is the fastest; *best and all stay shapes that can be set.
  * stag_set_dslash_shape pins *shape (host; its us is ignored) for the key; shape NULL or shape->wg = 0
  * removes the entry; a combination stag_shape rules out is STAG_ERR_ARG.  The table is process-wide;
  * stag_tune_cache_save / _load write and read it as JSON (path: a host C string). */
