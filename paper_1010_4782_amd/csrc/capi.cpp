@@ -205,16 +205,23 @@ struct OpCall {
   RingEntry e{};
   bool ring = false;
 };
-stag_status op_begin(stag_lattice_s* L, int nrhs, const double* mass, void* const* vec_override, int prec,
-                     hipStream_t st, OpCall& c, const Geo* geo_override = nullptr) {
+void op_shape(const stag_lattice_s* L, int nrhs, void* const* vec_override, int prec, const Geo* geo_override,
+              OpCall& c) {
   c.pd = op_problem(L, nrhs, vec_override, geo_override);
   op_sizes(c.pd, c.bh);
   c.sh = lookup_shape(c.bh, single_key(c.bh, L, prec), prec);
-  c.ring = nrhs > kInlineRhs || c.sh.order == 2;
+}
+stag_status op_table(stag_lattice_s* L, const double* mass, hipStream_t st, OpCall& c) {
+  c.ring = c.pd.nrhs > kInlineRhs || c.sh.order == 2;
   if (c.ring) return ring_batch(L, c.pd, mass, st, c.bh, c.e);
   c.bh.inl = &c.pd;
   c.bh.inl_mass = mass;
   return STAG_OK;
+}
+stag_status op_begin(stag_lattice_s* L, int nrhs, const double* mass, void* const* vec_override, int prec,
+                     hipStream_t st, OpCall& c) {
+  op_shape(L, nrhs, vec_override, prec, nullptr, c);
+  return op_table(L, mass, st, c);
 }
 stag_status op_end(stag_lattice_s* L, const OpCall& c, hipStream_t st) {
   return c.ring ? ring_release(L->ctl, c.e, st) : STAG_OK;
@@ -235,20 +242,17 @@ stag_status low_or_full_dslash(stag_lattice_s* lat, int out_parity, const void* 
     ov[V_D] = static_cast<char*>(lat->io_lo[0].ptr) + first * vb;
   }
   OpCall c;
-  stag_status s = op_begin(lat, nrhs, nullptr, ov, prec, st, c, geo);
-  if (s != STAG_OK) return s;
-  if (c.sh.order == 2) {
+  op_shape(lat, nrhs, ov, prec, geo, c);
+  const bool streaming = c.sh.order == 2;
+  if (streaming) {
     STAG_HIP_TRY(lat->io_lo[1].ensure(vb * out_sites * nrhs));
-    // the table is already on its way: point it at the low-precision output
-    ov[V_T] = lat->io_lo[1].ptr;
-    s = op_end(lat, c, st);
-    if (s == STAG_OK) s = op_begin(lat, nrhs, nullptr, ov, prec, st, c, geo);
-    if (s != STAG_OK) return s;
+    c.pd.vec[V_T] = lat->io_lo[1].ptr;
   }
-  const bool wide = prec != STAG_F64 && c.sh.order != 2;
+  stag_status s = op_table(lat, nullptr, st, c);
+  if (s != STAG_OK) return s;
+  const bool wide = prec != STAG_F64 && !streaming;
   STAG_HIP_TRY(launch_dslash(c.bh, prec, wide ? EPI_WIDE : EPI_PLAIN, out_parity, V_D, V_T, 0, 0, 3, c.sh, st));
-  if (prec != STAG_F64 && !wide)
-    STAG_HIP_TRY(launch_convert_to_f64(prec, lat->io_lo[1].ptr, out, out_sites * nrhs, st));
+  if (streaming) STAG_HIP_TRY(launch_convert_to_f64(prec, lat->io_lo[1].ptr, out, out_sites * nrhs, st));
   return op_end(lat, c, st);
 }
 

@@ -42,3 +42,36 @@ def test_tuner_keeps_the_default_where_it_is_the_fastest(gpu_lib, tmp_path):
     assert torch.equal(lat.dslash(x, 1), ref)
     lat.set_dslash_shape("f64", nrhs, 0)
     assert saved_shape(tmp_path, "p0:28x28x28x96/12") is None
+
+
+def test_time_streaming_call_fills_its_table_once(gpu_lib):
+    """The nodes a stream capture records of a call with a pinned time-streaming shape (the graph is never
+    launched): the input's conversion, one copy of the table, the operator, the output's conversion."""
+    import ctypes as C
+
+    dims, nrhs = (4, 4, 8, 4), 8
+    print(f"time-streaming table {dims} x {nrhs}", flush=True)
+    lat = setup(dims, 35, precs=("f64", "f16"))
+    x = gaussian_source_device(dims, 36, nrhs)
+    ref = lat.dslash(x, 1, prec="f16")
+    lat.set_dslash_shape("f16", nrhs, 64, 8, 0, 2, 1)
+    out = lat.dslash(x, 1, prec="f16")  # its workspace and the ring exist from here on
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref)
+    hip = gpu_lib  # the HIP runtime that the library is linked with
+    hip.hipGetLastError.argtypes = []
+    hip.hipStreamBeginCapture.argtypes = [C.c_void_p, C.c_int]
+    hip.hipStreamEndCapture.argtypes = [C.c_void_p, C.POINTER(C.c_void_p)]
+    hip.hipGraphGetNodes.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(C.c_size_t)]
+    hip.hipGraphDestroy.argtypes = [C.c_void_p]
+    side = torch.cuda.Stream()
+    graph, n = C.c_void_p(), C.c_size_t(0)
+    assert hip.hipStreamBeginCapture(side.cuda_stream, 2) == 0  # relaxed mode
+    lat.dslash(x, 1, prec="f16", out=out, stream=side)
+    assert hip.hipStreamEndCapture(side.cuda_stream, C.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, C.byref(n)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    lat.set_dslash_shape("f16", nrhs, 0)
+    lat.close()
+    hip.hipGetLastError()  # waiting for an event whose record was captured is an error that nothing else should see
+    assert n.value == 4, n.value
