@@ -18,6 +18,7 @@
 // either way, and a breakdown is in the sum they all form.
 #include "device.h"
 #include "launch.h"
+#include "wide_grid.h"
 
 namespace stag {
 
@@ -208,8 +209,6 @@ __global__ __launch_bounds__(kMaxWG) void k_xd(Batch B, Scal* next, int x_id, in
 // iteration.  An iteration takes, general -> wide: 24^3x48 FP16 112.8 -> 106.2 us, FP64 272 -> 266; 20^3x40 x 4
 // FP16 123.1 -> 115.9; 32^3x64 FP32 497 -> 490; 28^3x96 FP16 270.1 -> 267.9.  With 512 workgroups the sums cost
 // more than the second workgroup per CU gives: 109.9 us (24^3x48 FP16), 274.5 (28^3x96).
-constexpr int kWideWG = 1024;
-constexpr int kWideGrid = 256;    // one per CU
 constexpr int kWideUnroll = 24;   // partials a lane has in flight
 
 __device__ __forceinline__ double wide_sum(const double* src, int n, double* lds /* >= 16 */) {
@@ -379,17 +378,17 @@ __global__ __launch_bounds__(kWideWG) void k_xd_wide(Batch B, Scal* next, int x_
 
 int blocks_of(const Batch& B) { return B.block_start[B.nprob]; }
 
-// Workgroups of a wide launch: as many as give every one of them the same number of tiles, kWideGrid at most.
 Batch wide_batch(const BatchHost& bh) {
   Batch B = make_batch(bh, kWideWG, 1);
-  const int per = ceil_div(blocks_of(B), kWideGrid);
+  int slots[kMaxProb];
+  for (int p = 0; p < B.nprob; ++p) slots[p] = bh.probs[p].nrhs;
+  const int per = wide_tiles(B.tiles, slots, B.nprob);
   for (int p = 0; p < B.nprob; ++p) {
-    B.groups[p] = ceil_div(ceil_div(bh.probs[p].half, kWideWG), per);
-    B.block_start[p + 1] = B.block_start[p] + B.groups[p] * bh.probs[p].nrhs;
+    B.groups[p] = per ? ceil_div(B.tiles[p], per) : 0;  // none fit: refused below
+    B.block_start[p + 1] = B.block_start[p] + B.groups[p] * slots[p];
   }
   return B;
 }
-
 
 }  // namespace
 
@@ -397,7 +396,7 @@ hipError_t launch_fused_resid(const BatchHost& bh, bool wide, int prec, int dot_
                               hipStream_t st) {
   const Batch B = wide ? wide_batch(bh) : make_batch(bh, kMaxWG, 1);
   const int nb = blocks_of(B);
-  if (nb == 0) return hipSuccess;
+  if (nb == 0) return bh.nslots ? hipErrorInvalidValue : hipSuccess;
   const int r_id = prec == P64 ? V_R : V_RL;
 #define STAG_RESID(P)                                                                                  \
   if (wide)                                                                                            \
@@ -418,7 +417,7 @@ hipError_t launch_fused_xd(const BatchHost& bh, bool wide, Scal* next, int prec,
                            int hist_stride, hipStream_t st) {
   const Batch B = wide ? wide_batch(bh) : make_batch(bh, kMaxWG, 1);
   const int nb = blocks_of(B);
-  if (nb == 0) return hipSuccess;
+  if (nb == 0) return bh.nslots ? hipErrorInvalidValue : hipSuccess;
   const int r_id = prec == P64 ? V_R : V_RL;
 #define STAG_XD(P, PX)                                                                                 \
   if (wide)                                                                                            \

@@ -12,6 +12,7 @@
 #include <set>
 
 #include "runtime.h"
+#include "wide_grid.h"
 
 namespace stag {
 
@@ -121,11 +122,15 @@ Path iteration_path(const Run& R) {
   if (R.profile_every > 0) return kGeneral;
   int most = 0;
   long sites = 0;
+  std::vector<int> tiles, slots;
   for (const HostProb& p : R.bh.probs) {
     most = std::max(most, ceil_div(p.half, std::min(partial_wg(R.shape), kVecWG)));
     sites += (long)p.half * p.nrhs;
+    tiles.push_back(ceil_div(p.half, kWideWG));
+    slots.push_back(p.nrhs);
   }
-  return most <= kFusedTiles ? kSmall : (sites <= kWideSites ? kWide : kGeneral);
+  if (most <= kFusedTiles) return kSmall;
+  return sites <= kWideSites && wide_tiles(tiles.data(), slots.data(), (int)tiles.size()) ? kWide : kGeneral;
 }
 
 // n CG iterations (x accumulated in precision x_prec at x_id), from and to the state between iterations.
