@@ -111,26 +111,38 @@ hipError_t iteration(Run& R, int x_prec, int x_id, double* d_hist) {
 }
 
 // How a batch's iterations run: on the fused kernels (cg_fused.hip), which add the partials of a reduction in
-// every workgroup, or (kGeneral) with the reductions as launches of their own.  The wide kernels hold one
-// workgroup per CU and lose to the general ones where a launch is bound by memory rather than by latency: an FP16
-// iteration of 24^3x48 takes 106.2 us against 112.8 with one right-hand side (332 thousand sites in the launch),
-// 215.7 against 217.7 with four, 468.6 against 458.0 with twelve; 32^3x64 with two (2.1 million) 401.4 against
-// 403.3.  Sampled profiles keep the general path.
+// every workgroup, or (kGeneral) with the reductions as launches of their own.  us an iteration, fused and general:
+//  * The one-tile kernels read a slot's partials once per 256 sites.  FP64 gains up to 64 right-hand sides of
+//    16^3x32 (996 and 1016), FP32 does not lose (603 and 604); FP16, whose vectors are the smallest, does from
+//    64 MiB of partials an iteration on (24: 191 and 193, 32: 257 and 254, 64: 464 and 444).
+//  * The wide kernels hold one workgroup per CU and are no faster where a launch is bound by memory rather than by
+//    latency (2^21 sites: 32^3x64 with two right-hand sides, FP16, 401 and 403; 24^3x48 with 6, 304 and 305).
+//    With many right-hand sides the tiles divide less evenly over the CUs, which FP64 still gains from (16^3x40
+//    with 22: 460 and 463) and FP32 and FP16 do not (FP32, 17: 250 and 246, 22: 324 and 314; FP16, 22: 259 and
+//    256; 20^3x40 with 13: 355 and 357, 266 and 271).
+// Sampled profiles keep the general path.
 constexpr long kWideSites = 1L << 21;
+constexpr int kWideSlotsLow = 16;
+constexpr double kPartialBytesF16 = 64.0 * 1024 * 1024;
 enum Path { kGeneral, kSmall, kWide };
 Path iteration_path(const Run& R) {
   if (R.profile_every > 0) return kGeneral;
   int most = 0;
   long sites = 0;
+  double partials = 0.0;
   std::vector<int> tiles, slots;
+  const int dot_wg = partial_wg(R.shape);
   for (const HostProb& p : R.bh.probs) {
-    most = std::max(most, ceil_div(p.half, std::min(partial_wg(R.shape), kVecWG)));
+    most = std::max(most, ceil_div(p.half, std::min(dot_wg, kVecWG)));
     sites += (long)p.half * p.nrhs;
+    partials += 8.0 * p.nrhs * ceil_div(p.half, kVecWG) * ceil_div(p.half, dot_wg);
     tiles.push_back(ceil_div(p.half, kWideWG));
     slots.push_back(p.nrhs);
   }
-  if (most <= kFusedTiles) return kSmall;
-  return sites <= kWideSites && wide_tiles(tiles.data(), slots.data(), (int)tiles.size()) ? kWide : kGeneral;
+  const bool low = R.prec != P64;
+  if (most <= kFusedTiles) return R.prec == P16 && partials >= kPartialBytesF16 ? kGeneral : kSmall;
+  if (sites > kWideSites || (low && R.bh.nslots > kWideSlotsLow)) return kGeneral;
+  return wide_tiles(tiles.data(), slots.data(), (int)tiles.size()) ? kWide : kGeneral;
 }
 
 // n CG iterations (x accumulated in precision x_prec at x_id), from and to the state between iterations.
