@@ -54,6 +54,12 @@ double slice_bytes(const BatchHost& bh, int prec) {
   return m;
 }
 
+// Whether FP16 below 2 MiB of colour vectors per time slice takes z blocks too, at r right-hand sides per lane.
+bool f16_z_blocks(const BatchHost& bh, int r) {
+  const bool power_of_two = (bh.max_half & (bh.max_half - 1)) == 0;
+  return r <= 2 && bh.max_half >= 3 << 18 && !power_of_two && slice_bytes(bh, P16) > 128.0 * 1024;
+}
+
 // Without a tuned entry.  64-site workgroups (128 for FP16 at 8 RHS per lane); every choice gives the same bits.
 //  * Right-hand sides per lane: up to 4, where a lane's registers still leave two or three waves per SIMD; 8 for
 //    FP16 with 18-real three-hop links (no third-row rebuild), and for FP32 and FP64 from 2^18 sites of one
@@ -72,7 +78,12 @@ double slice_bytes(const BatchHost& bh, int prec) {
 //    that sweep t through one XCD's share: z blocks where the lattice allows them (32^3x64 x 8: FP64 781 us
 //    against 989, FP32 415 and 462), else the XCD sweep (28^3x96: FP64 x 12 RHS, 6.3 MB a slice, 1154 us against
 //    1398; FP32 x 8, 2.1 MB, 591 and 626; at 2.0 MB, 24^3x48 FP32 x 12, 264 and 260).  FP32 and FP64 take z blocks
-//    from 2^18 sites on (32^3x64 x 1: 349 us against 356 and 175 against 183; FP16 x 2: 108 against 103).
+//    from 2^18 sites on (32^3x64 x 1: 349 us against 356 and 175 against 183).  FP16 takes
+//    them with one or two per lane from 3 x 2^18 sites on: an iteration of CG, z blocks and lattice order, 48^3x144
+//    x 1 1972 and 2049 us, 32^3x96 x 1 395 and 414, x 2 496 and 520, 32^3x48 x 2 267 and 283; below, 32^2x16x48
+//    x 1 119 and 115.  Not where the sites are a power of two (32^3x64 x 1 341 and 337, x 2 356 and 342, where
+//    32^3x72 has 303 and 323, 393 and 409), not with four per lane (32^3x96 717 and 715), and not with up to 128 KiB
+//    of vectors per slice (the operator, 16^3x512 x 4: 219 and 217).
 DslashShape heuristic(const BatchHost& bh, int prec) {
   constexpr int kLargeHalf = 1 << 18;
   const bool r8_f16 = prec == P16 && !bh.long12, large = bh.max_half >= kLargeHalf;
@@ -96,7 +107,7 @@ DslashShape heuristic(const BatchHost& bh, int prec) {
       break;
     }
   s.wg = prec == P16 && s.r == 8 ? 128 : 64;
-  s.order = sweep || (prec != P16 && large) ? 1 : 0;
+  s.order = sweep || (prec == P16 ? f16_z_blocks(bh, s.r) : large) ? 1 : 0;
   if (s.order && !dslash_shape_valid(bh, prec, s)) s.order = 0;
   if (!dslash_shape_valid(bh, prec, s)) s = DslashShape{64, 1, 0, 0};
   s.sweep = s.order == 0 && sweep;

@@ -75,3 +75,22 @@ def test_time_streaming_call_fills_its_table_once(gpu_lib):
     lat.close()
     hip.hipGetLastError()  # waiting for an event whose record was captured is an error that nothing else should see
     assert n.value == 4, n.value
+
+
+# z blocks below 2 MiB of colour vectors per slice: one or two per lane from 3 x 2^18 sites on; not where the sites
+# are a power of two, not with four, nor slices of up to 128 KiB, nor z extents that 8 does not divide
+@pytest.mark.parametrize("dims,nrhs,su3,order", [((32, 32, 32, 48), 1, True, 1), ((32, 32, 32, 46), 1, True, 0),
+                                                 ((32, 32, 24, 64), 2, False, 1), ((32, 32, 24, 62), 2, False, 0),
+                                                 ((32, 32, 32, 64), 1, False, 0), ((32, 32, 32, 64), 2, True, 0),
+                                                 ((32, 32, 24, 64), 4, False, 0), ((16, 16, 16, 384), 1, False, 0),
+                                                 ((32, 32, 28, 56), 2, True, 0)])
+def test_f16_tile_order_by_size(gpu_lib, dims, nrhs, su3, order):
+    print(f"FP16 tile order {dims} x {nrhs} su3 {su3}", flush=True)
+    lat = setup(dims, 37, precs=("f64", "f16"), long_su3=su3)
+    x = gaussian_source_device(dims, 39, nrhs)
+    _, info = lat.cg_solve(x, 0.5, prec="f16", max_iter=1, max_restarts=0, raise_on_fail=False)
+    assert info[0]["dslash_order"] == order
+    out = lat.dslash(x, 1, prec="f16")
+    lat.set_dslash_shape("f16", nrhs, 64, 1)
+    assert torch.equal(lat.dslash(x, 1, prec="f16"), out)
+    lat.set_dslash_shape("f16", nrhs, 0)
