@@ -65,7 +65,11 @@ bool f16_z_blocks(const BatchHost& bh, int r) {
 //    FP16 with 18-real three-hop links (no third-row rebuild), and for FP32 and FP64 from 2^18 sites of one
 //    parity on, where reading each link once is worth the one wave per SIMD it leaves (28^3x96 x 8: FP64 803 us
 //    against 994 at 4, FP32 534 and 616; 24^3x48: 276 and 280, 178 and 187; at 16^3x32 4 is faster, 48 and 57).
-//  * Fewer while that leaves less than two waves per SIMD (16^3x32 x 4: FP64 34 us at 2 per lane, 37 at 4).
+//  * Fewer while that leaves less than two waves per SIMD (16^3x32 x 4, FP32: 25 us at 2 per lane, 28 at 4).  An FP64
+//    launch holds one wave per SIMD, 1024 at once, and one that fits is not split over more (12^4 x 24: 20 us at 4
+//    per lane, 972 waves, 31 at 1, four rounds of waves; 10x14x18x22 x 8: 22 us at 4, 36 at 1; the normal operator of
+//    16^3x32 with 18-real links, x 2: 61 us at 2 per lane, 75 at 1, where a repeated one-parity operator, whose links
+//    stay in the 256 MB cache, takes 30 and 28).
 //  * Counts that are no multiple of 4 or 8 mask lanes of the last group instead of taking one or two per lane, where
 //    that leaves at most two thirds of the groups: links are read, and x, y neighbours found in L1, once per
 //    group.  28^3x96: 3 RHS FP64 739 -> 500 us, FP32 405 -> 313, FP16 247 -> 190; 5 RHS 982 -> 582, 609 -> 394,
@@ -99,7 +103,8 @@ DslashShape heuristic(const BatchHost& bh, int prec) {
   auto mostly_idle = [&](int r) {  // a last lane with half of its right-hand sides or more masked
     return std::any_of(bh.probs.begin(), bh.probs.end(), [&](const HostProb& p) { return (r - p.nrhs % r) % r >= r / 2; });
   };
-  while (s.r > 1 && waves(s.r) < 2048) s.r >>= 1;
+  auto one_round = [&](int r) { return prec == P64 && waves(r) <= 1024; };
+  while (s.r > 1 && waves(s.r) < 2048 && one_round(s.r) == one_round(s.r / 2)) s.r >>= 1;
   const long enough = prec == P64 ? 2048 : (prec == P32 ? 5120 : 7168);
   for (int r = std::min(rhs_most(bh), most); r > s.r && r >= (prec == P16 ? 4 : 2); r >>= 1)
     if (waves(r) >= enough && 3 * waves(r) <= 2 * waves(s.r) && !(r == 8 && mostly_idle(r))) {

@@ -94,3 +94,18 @@ def test_f16_tile_order_by_size(gpu_lib, dims, nrhs, su3, order):
     lat.set_dslash_shape("f16", nrhs, 64, 1)
     assert torch.equal(lat.dslash(x, 1, prec="f16"), out)
     lat.set_dslash_shape("f16", nrhs, 0)
+
+
+# an FP64 launch of at most 1024 waves is not split beyond that; waves at 4, 2 and 1 per lane: 324, 648, 1296; 972,
+# 1944; 4, 8, 16; 1536, 3072; -, 1024, 2048
+@pytest.mark.parametrize("dims,nrhs,per_lane", [((12, 12, 12, 12), 8, 2), ((12, 12, 12, 12), 24, 4), ((4, 4, 4, 2), 8, 1),
+                                                ((16, 16, 16, 48), 4, 2), ((16, 16, 16, 32), 2, 2)])
+def test_f64_right_hand_sides_per_lane(gpu_lib, dims, nrhs, per_lane):
+    print(f"FP64 per lane {dims} x {nrhs}", flush=True)
+    lat = setup(dims, 41, precs=("f64",))
+    x = gaussian_source_device(dims, 43, nrhs)
+    _, info = lat.cg_solve(x, 0.5, max_iter=1, max_restarts=0, raise_on_fail=False)
+    assert info[0]["dslash_rhs"] == per_lane
+    out = lat.dslash(x, 1)
+    for r in (0, nrhs - 1):
+        assert torch.equal(lat.dslash(x[r:r + 1].contiguous(), 1)[0], out[r])
