@@ -57,7 +57,7 @@ double slice_bytes(const BatchHost& bh, int prec) {
 // Whether FP16 below 2 MiB of colour vectors per time slice takes z blocks too, at r right-hand sides per lane.
 bool f16_z_blocks(const BatchHost& bh, int r) {
   const bool power_of_two = (bh.max_half & (bh.max_half - 1)) == 0;
-  return r <= 2 && bh.max_half >= 3 << 18 && !power_of_two && slice_bytes(bh, P16) > 128.0 * 1024;
+  return r <= 2 && bh.max_half >= 3 << 18 && !power_of_two;
 }
 
 // Without a tuned entry.  64-site workgroups (128 for FP16 at 8 RHS per lane); every choice gives the same bits.
@@ -86,8 +86,7 @@ bool f16_z_blocks(const BatchHost& bh, int r) {
 //    them with one or two per lane from 3 x 2^18 sites on: an iteration of CG, z blocks and lattice order, 48^3x144
 //    x 1 1972 and 2049 us, 32^3x96 x 1 395 and 414, x 2 496 and 520, 32^3x48 x 2 267 and 283; below, 32^2x16x48
 //    x 1 119 and 115.  Not where the sites are a power of two (32^3x64 x 1 341 and 337, x 2 356 and 342, where
-//    32^3x72 has 303 and 323, 393 and 409), not with four per lane (32^3x96 717 and 715), and not with up to 128 KiB
-//    of vectors per slice (the operator, 16^3x512 x 4: 219 and 217).
+//    32^3x72 has 303 and 323, 393 and 409), and not with four per lane (32^3x96 717 and 715).
 DslashShape heuristic(const BatchHost& bh, int prec) {
   constexpr int kLargeHalf = 1 << 18;
   const bool r8_f16 = prec == P16 && !bh.long12, large = bh.max_half >= kLargeHalf;
