@@ -100,14 +100,18 @@ __device__ __forceinline__ NetView net_side(const NetLaunch& l, int& cb) {
   return net_view(l, l.n == 2 && (j & 1));
 }
 
-// The same with one contiguous range of whole 64-site link blocks per XCD, net_range_len sites.
+// The same with one contiguous range of whole 64-site link blocks per XCD, net_range_len sites, and one side after
+// the other: the first layer's even side reads its own sites only, and in between the odd side's workgroups it was
+// in their way.  A call of two layers with 2 channels at 24^3x48 takes 103 us, 114 interleaved (111 as two
+// launches), with 8 channels 148 and 164.
 __host__ __device__ inline int net_range_len(int half) { return ceil_div(half, 8 * kWave) * kWave; }
 __device__ __forceinline__ NetView net_range_side(const NetLaunch& l, int& cb) {
   const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int half = l.a[0].g.half, n = net_range_len(half);
-  const int i = (l.n == 2 ? j >> 1 : j) * blockDim.x + threadIdx.x;
-  cb = i < n && xcd * n + i < half ? xcd * n + i : -1;
-  return net_view(l, l.n == 2 && (j & 1));
+  const int half = l.a[0].g.half, n = net_range_len(half), per = n / kNetVecWG;
+  const bool second = l.n == 2 && j < per;
+  const int i = (l.n == 2 && !second ? j - per : j) * kNetVecWG + threadIdx.x;
+  cb = xcd * n + i < half ? xcd * n + i : -1;
+  return net_view(l, second);
 }
 
 // Transported colour vectors of all input channels along direction d (1..8) for the site s.
