@@ -386,6 +386,11 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
   // staged (28^3x96 425 and 433).  With 12-real links (137 us staged, 142 piecewise) and in FP32 (101 and 103)
   // staging is faster there too.
   constexpr bool kStaged = !LDS && !(P == P64 && R == 1 && !C12);
+  // With 12-real links the launch that ends a CG iteration's operator stores piecewise too from 2^19 sites on
+  // (an iteration of 28^3x96 826 us against 835, 26^3x60 416 and 421; below, 24^3x48 270 and 268).
+  constexpr int kPiecewiseFrom = 1 << 19;
+  constexpr bool kEither = kStaged && P == P64 && R == 1 && (EPI == EPI_XPAY_DOT || EPI == EPI_RESID);
+  const bool piecewise = kEither && g.half >= kPiecewiseFrom;  // uniform
   char* out = vec(out_id) + (long)r0 * rstride;
   if (EPI == EPI_PLAIN) {
 #pragma unroll
@@ -413,7 +418,10 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
 #pragma unroll
       for (int c = 0; c < 3; ++c) o[c] = Cx<T>{a * xv[c].re - acc[r][c].re, a * xv[c].im - acc[r][c].im};
     }
-    store_out<P, kStaged>(out + r * rstride, cb_raw, live, g.half, o);
+    if (piecewise)
+      store_out<P, false>(out + r * rstride, cb_raw, live, g.half, o);
+    else
+      store_out<P, kStaged>(out + r * rstride, cb_raw, live, g.half, o);
     if (live) {
       if (EPI == EPI_XPAY_DOT) {
 #pragma unroll
