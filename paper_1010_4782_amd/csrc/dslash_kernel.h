@@ -184,19 +184,35 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
   using T = typename RealOf<P>::T;
   __shared__ double lds[R * 4];
   const Batch& B = A.B;
+  // Asked for one by one where a branch first needs them, the launch's parameters are a chain of round trips to
+  // memory in front of every wave (28^3x96 x 2, FP16: a launch that finds every right-hand side stopped takes 6.9
+  // us).  FP32 and FP16 ask for them at once: an FP16 iteration of 8^4 takes 32 us instead of 37, of 16^3x32 x 4
+  // 77 instead of 83, of 28^3x96 303 instead of 308.  FP64 is better off with the chain on large lattices
+  // (28^3x96 x 2, 18-real links: 1155 us an iteration, 1190 without).
+  int nblk = gridDim.x, wg = blockDim.x, inl_arg = A.inl, nprob = B.nprob, groups = B.groups[0];
+  if constexpr (P != P64) asm volatile("" : "+s"(nblk), "+s"(wg), "+s"(nzb), "+s"(inl_arg), "+s"(nprob), "+s"(groups));
   const bool sweep = nzb < 0;
-  const int bid = sweep ? (int)(blockIdx.x >> 3) : xcd_remap(blockIdx.x, gridDim.x);
-  const bool inl = A.inl != 0;
-  const int p = inl ? 0 : find_problem(B, bid);
+  const int bid = sweep ? (int)(blockIdx.x >> 3) : xcd_remap(blockIdx.x, nblk);
+  const bool inl = inl_arg != 0;
+  int p = 0, start = 0;
+  if (P == P64) {
+    p = inl ? 0 : find_problem(B, bid);
+  } else if (nprob > 1) {
+    p = find_problem(B, bid);
+  }
+  if (P == P64 || nprob > 1) {
+    start = B.block_start[p];
+    groups = B.groups[p];
+  }
   const cptr<ProbDev> pd = inl ? kernarg_problem() : (cptr<ProbDev>)(B.probs + p);
+  int nrhs = pd->nrhs, slot0 = pd->slot0;
   const Geo g = load_geo(pd);
+  if constexpr (P != P64) asm volatile("" : "+s"(nrhs), "+s"(slot0));
   auto vec = [&](int id) { return reinterpret_cast<char*>(pd->vec[id]); };
-  const int local = bid - B.block_start[p];
-  const int groups = B.groups[p];
+  const int local = bid - start;
   const int pos = local / groups;
   const int r0 = (local - pos * groups) * R;
-  const int nrhs = pd->nrhs, slot0 = pd->slot0;
-  const int tile = sweep ? xcd_sweep_tile(pos, g, blockDim.x) : (nzb ? xcd_block_tile(pos, g, blockDim.x, nzb) : pos);
+  const int tile = sweep ? xcd_sweep_tile(pos, g, wg) : (nzb ? xcd_block_tile(pos, g, wg, nzb) : pos);
   if (tile < 0) return;  // uniform: an unused position of the sweep
 
   bool on[R];
@@ -208,7 +224,7 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
   }
   if (!any) return;  // uniform over the workgroup
 
-  const int cb_raw = tile * blockDim.x + threadIdx.x;
+  const int cb_raw = tile * wg + threadIdx.x;
   const bool live = cb_raw < g.half;
   const int cb = live ? cb_raw : g.half - 1;  // dead lanes read a valid site and store nothing
   const Site s = site_of(cb, out_par, g);
@@ -236,8 +252,8 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
     for (int c = 0; c < 3; ++c) acc[r][c] = Cx<T>{T(0), T(0)};
 
   // LDS window: sites [w0, w0 + wn) of every active RHS, 8-byte units, loaded by the whole workgroup
-  const int w0 = tile * (int)blockDim.x - window_margin(g.Xh);
-  const int wn = (int)blockDim.x + 2 * window_margin(g.Xh);
+  const int w0 = tile * wg - window_margin(g.Xh);
+  const int wn = wg + 2 * window_margin(g.Xh);
   constexpr int SB = spinor_bytes(P);
   if constexpr (LDS) {
     const int units = wn * SB / 8;
@@ -247,7 +263,7 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
       // window sites outside [0, in_half) are never read back: every neighbour index is in range
       const char* src = in + r * rstride_in;
       char* dst = dslash_window + r * wn * SB;
-      for (int u = threadIdx.x; u < units; u += blockDim.x) {
+      for (int u = threadIdx.x; u < units; u += wg) {
         const int site = w0 + (u * 8) / SB;
         if (site >= 0 && site < g.in_half)
           *reinterpret_cast<u2v*>(dst + u * 8) = *as_global<u2v>(src + (long)w0 * SB + (long)u * 8);
