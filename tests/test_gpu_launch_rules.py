@@ -1,11 +1,11 @@
 """Launch shapes chosen by size or by the tuner: which one runs, and that it leaves every bit alone."""
 import json
 
+import numpy as np
 import pytest
 import torch
 
-from stag_inputs import (fat_field, fat_field_device, gaussian_source, gaussian_source_device, random_su3_field,
-                         random_su3_field_device)
+from stag_inputs import fat_field_device, gaussian_source_device, random_su3_field_device
 
 pytestmark = pytest.mark.gpu
 NAIK = -1.0 / 24.0
@@ -109,3 +109,70 @@ def test_f64_right_hand_sides_per_lane(gpu_lib, dims, nrhs, per_lane):
     out = lat.dslash(x, 1)
     for r in (0, nrhs - 1):
         assert torch.equal(lat.dslash(x[r:r + 1].contiguous(), 1)[0], out[r])
+
+
+# more than 256 tiles of 1024 sites in all, so that every workgroup of the wide CG kernels walks several: 151 ragged
+# ones for each of 3 right-hand sides, and 69 for each of 5 beside a single one
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
+def test_wide_cg_walks_are_the_general_iterations(gpu_lib, prec):
+    from paper_1010_4782_amd.stagcg import cg_solve_batch
+
+    dims, nrhs = (22, 18, 26, 30), 3
+    print(f"wide CG walk {dims} x {nrhs} {prec}", flush=True)
+    lat = setup(dims, 45, long_su3=True)
+    b = gaussian_source_device(dims, 47, nrhs)
+    mass = [0.2 + 0.2 * r for r in range(nrhs)]  # slots stop at different iterations
+    out = []
+    for profile in (0, 1000):
+        hist = np.zeros((nrhs, 40, 2))
+        x, info = lat.cg_solve(b, mass, prec=prec, profile=profile, history_len=40, history=hist)
+        out.append((x, hist, [(i["iters"], i["n_reliable"], i["true_resid"]) for i in info]))
+    assert torch.equal(out[0][0], out[1][0]) and out[0][2] == out[1][2]
+    np.testing.assert_array_equal(out[0][1], out[1][1])
+    shapes = [((14, 18, 26, 22), 5), ((2, 4, 4, 2), 2)]
+    lats = [setup(d, 49 + i, long_su3=True) for i, (d, _) in enumerate(shapes)]
+    bs = [gaussian_source_device(d, 51 + i, n) for i, (d, n) in enumerate(shapes)]
+    out = []
+    for profile in (0, 1000):
+        xs, info = cg_solve_batch([(l, v, 0.3, None) for l, v in zip(lats, bs)], prec=prec, profile=profile)
+        out.append((xs, [(i["iters"], i["n_reliable"], i["true_resid"]) for i in info]))
+    assert all(torch.equal(u, v) for u, v in zip(out[0][0], out[1][0])) and out[0][1] == out[1][1]
+
+
+def test_sweep_over_several_lattices_is_the_lattice_order(gpu_lib):
+    """A batch whose largest slice passes 2 MiB sweeps t per XCD over all its lattices, slices that eight does not
+    divide and a lattice smaller than the XCDs' shares among them; each solve has the bits of its solve alone in
+    lattice order."""
+    from paper_1010_4782_amd.stagcg import cg_solve_batch
+
+    shapes = [((22, 18, 14, 6), 16), ((6, 10, 6, 10), 3), ((2, 2, 2, 2), 1)]
+    print(f"sweep over {shapes}", flush=True)
+    lats = [setup(d, 53 + i) for i, (d, _) in enumerate(shapes)]
+    bs = [gaussian_source_device(d, 57 + i, n) for i, (d, n) in enumerate(shapes)]
+    xs, info = cg_solve_batch([(l, b, 0.4, None) for l, b in zip(lats, bs)])
+    k = 0
+    for lat, b, x, (dims, n) in zip(lats, bs, xs, shapes):
+        lat.set_dslash_shape("f64", n, 64, 1)
+        y, one = lat.cg_solve(b, 0.4)
+        lat.set_dslash_shape("f64", n, 0)
+        assert torch.equal(x, y) and [i["iters"] for i in one] == [i["iters"] for i in info[k:k + n]], dims
+        k += n
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
+@pytest.mark.parametrize("su3", [False, True])
+def test_sweep_on_a_slab_is_the_whole_lattice(gpu_lib, prec, su3):
+    """Slabs whose slices pass 2 MiB of colour vectors and whose z extent rules out z blocks: the XCD sweep, the
+    single right-hand side in lattice order."""
+    dims, nrhs = (28, 26, 22, 8), 18
+    print(f"slab sweep {dims} x {nrhs} {prec} su3 {su3}", flush=True)
+    lat = setup(dims, 61, precs=("f64", prec), long_su3=su3)
+    S, Lt = dims[0] * dims[1] * dims[2] // 2, dims[3]
+    assert S * nrhs * {"f64": 48, "f32": 24, "f16": 16}[prec] >= 2 << 20
+    b = gaussian_source_device(dims, 63, nrhs)
+    for par in (0, 1):
+        ref = torch.cat([lat.dslash(b[r:r + 1].contiguous(), par, prec=prec) for r in range(nrhs)])
+        for t0, lt in ((0, 2), (2, 6), (4, 4)):
+            rows = torch.cat([torch.arange(((t0 + k) % Lt) * S, ((t0 + k) % Lt + 1) * S) for k in range(-3, lt + 3)])
+            out = lat.dslash_slab(b[:, rows.cuda(), :].contiguous(), par, t0, lt, prec=prec)
+            assert torch.equal(out, ref[:, t0 * S:(t0 + lt) * S, :]), (par, t0, lt)
