@@ -356,20 +356,19 @@ __device__ __forceinline__ WgradBlock wgrad_block(int nblk, int nd, int nside) {
   return WgradBlock{xcd * (nblk >> 3) + j / per, k % nd, k / nd};
 }
 
-// Weight gradient, one direction d (blockIdx.y), all G = C_out output channels:
+// Weight gradient, one direction d per workgroup (wgrad_block), all output channels:
 //   partial[p][d][c][c'] = sum_n sum_a G_c(n)_a conj((T_d psi_c')(n)_a)
 // over the output sites of parity a.out_par; each block walks sites with a grid stride and
 // writes one partial (complex, FP64) per (d, c, c') for a fixed-order second stage.
-template <int CIN, int COUT, int G>
+template <int CIN, int COUT>
 __global__ __launch_bounds__(256) void k_net_wgrad(NetLaunch l, double* partial, int nblk) {
   const WgradBlock wb = wgrad_block(nblk, 9, l.n);
   const NetView a = net_view(l, wb.side != 0);
   const float2* gy = a.gy;
   const int b = wb.b, d = wb.d;
-  constexpr int cg = 0;
-  Cx<float> acc[G][CIN];
+  Cx<float> acc[COUT][CIN];
 #pragma unroll
-  for (int c = 0; c < G; ++c)
+  for (int c = 0; c < COUT; ++c)
 #pragma unroll
     for (int ci = 0; ci < CIN; ++ci) acc[c][ci] = Cx<float>{0.f, 0.f};
   const bool have = d == 0 ? a.in_same != nullptr : a.in_other != nullptr;
@@ -382,10 +381,10 @@ __global__ __launch_bounds__(256) void k_net_wgrad(NetLaunch l, double* partial,
       } else {
         transported<CIN>(a, s, cb >> 6, cb & 63, d, t);
       }
-      Cx<float> gvs[G][3];
-      load_channels<COUT, G>(gy, a.g.half, cb, cg * G, gvs);
+      Cx<float> gvs[COUT][3];
+      load_channels<COUT, COUT>(gy, a.g.half, cb, 0, gvs);
 #pragma unroll
-      for (int c = 0; c < G; ++c) {
+      for (int c = 0; c < COUT; ++c) {
         const Cx<float>* gv = gvs[c];
 #pragma unroll
         for (int ci = 0; ci < CIN; ++ci)
@@ -403,14 +402,13 @@ __global__ __launch_bounds__(256) void k_net_wgrad(NetLaunch l, double* partial,
   // block reduction, one (c, c') pair at a time, in FP64
   __shared__ double lds[2 * 4];
 #pragma unroll
-  for (int c = 0; c < G; ++c)
+  for (int c = 0; c < COUT; ++c)
 #pragma unroll
     for (int ci = 0; ci < CIN; ++ci) {
       double v[2] = {(double)acc[c][ci].re, (double)acc[c][ci].im};
       block_sum<2>(v, lds);
       if (threadIdx.x == 0) {
-        const int co = cg * G + c;
-        const long idx = ((((long)a.out_par * 9 + d) * COUT + co) * CIN + ci) * nblk + b;
+        const long idx = ((((long)a.out_par * 9 + d) * COUT + c) * CIN + ci) * nblk + b;
         partial[2 * idx] = v[0];
         partial[2 * idx + 1] = v[1];
       }
@@ -418,7 +416,7 @@ __global__ __launch_bounds__(256) void k_net_wgrad(NetLaunch l, double* partial,
     }
 }
 
-// Weight gradient on the matrix cores, two directions d per workgroup (blockIdx.y = d / 2):
+// Weight gradient on the matrix cores, two directions d per workgroup (wgrad_block):
 //   P[c][c'] = sum_n sum_a G_c(n)_a conj(X_d,c'(n)_a),  X_d = T_d psi (or psi for d = 0),
 // as a real GEMM over the inner index k = 2 n + part (n = 3 site + colour) with rows i = 2c + {re, im}:
 //   A[2c][(n,0)] = Re G, A[2c][(n,1)] = Im G, A[2c+1][(n,0)] = Im G, A[2c+1][(n,1)] = -Re G,
@@ -657,7 +655,7 @@ hipError_t launch_net_wgrad(const NetLaunch& l, double* partial, int cin, int co
   if (nblk % 8) return hipErrorInvalidValue;
 #define STAG_NET_WG(I, O)                                                          \
   if (cin == I && cout == O) {                                                     \
-    k_net_wgrad<I, O, O><<<nblk * 9 * l.n, 256, 0, st>>>(l, partial, nblk);          \
+    k_net_wgrad<I, O><<<nblk * 9 * l.n, 256, 0, st>>>(l, partial, nblk);           \
     return hipGetLastError();                                                      \
   }
 #define STAG_NET_WG_MFMA(I, O)                                                     \
