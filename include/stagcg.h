@@ -115,9 +115,11 @@ typedef struct {
   int32_t dslash_prec;       /* precision of the timed Dslash launches (inner iteration precision) */
   double dslash_sites;       /* profile>0: output sites x RHS processed per timed launch, averaged */
   int32_t dslash_wg;         /* launch shape used by the inner-iteration Dslash: sites per workgroup */
-  int32_t dslash_rhs;        /* ... right-hand sides per lane */
+  int32_t dslash_rhs;        /* ... right-hand sides per lane (the untuned default may mask some of the last lane:
+                                need not divide nrhs) */
   int32_t dslash_lds;        /* ... LDS staging of the x/y neighbour window (1) or not (0) */
-  int32_t dslash_order;      /* ... the tile order (0 lattice order, 1 XCD blocks, 2 time streaming) */
+  int32_t dslash_order;      /* ... the tile order (0 lattice order, also where each XCD sweeps t, 1 XCD blocks,
+                                2 time streaming) */
   int32_t dslash_chunks;     /* ... and its z blocks per XCD (order 1) or time chunks (order 2) */
 } stag_cg_info;
 

@@ -1,10 +1,10 @@
 // Autotuner for the Dslash launch shape: workgroup size (sites per workgroup),
 // right-hand sides per lane, LDS staging of the x/y neighbour window and the
 // tile order (lattice order, or XCD blocks with their number of z blocks per XCD), and, for FP16
-// batches of 8k right-hand sides, the time-streaming kernel with its number of time chunks.  Candidates are timed with HIP events on the caller's
-// stream on the real buffers of the call; winners are kept per key
-// (lattice shapes, right-hand sides, storage precision) in memory and can be saved
-// to / loaded from a small JSON file.
+// batches of 8k right-hand sides, the time-streaming kernel with its number of time chunks; and the untuned
+// default, whatever it is.  Candidates are timed with HIP events on the caller's stream on the real buffers of
+// the call; winners are kept per key (lattice shapes, right-hand sides, storage precision) in memory and can be
+// saved to / loaded from a small JSON file.
 #include <algorithm>
 #include <cstdio>
 #include <fstream>
@@ -61,19 +61,21 @@ bool f16_z_blocks(const BatchHost& bh, int r) {
 }
 
 // Without a tuned entry.  64-site workgroups (128 for FP16 at 8 RHS per lane); every choice gives the same bits.
-//  * Right-hand sides per lane: up to 4, where a lane's registers still leave two or three waves per SIMD; 8 for
-//    FP16 with 18-real three-hop links (no third-row rebuild), and for FP32 and FP64 from 2^18 sites of one
-//    parity on, where reading each link once is worth the one wave per SIMD it leaves (28^3x96 x 8: FP64 803 us
-//    against 994 at 4, FP32 534 and 616; 24^3x48: 276 and 280, 178 and 187; at 16^3x32 4 is faster, 48 and 57).
+//  * Right-hand sides per lane: up to 4; 8 for FP16 with 18-real three-hop links, and for FP32 and FP64 from 2^18
+//    sites of one parity on, where each link is read once for all of them (28^3x96 x 8: FP64 803 us against 994 at
+//    4, FP32 534 and 616; 24^3x48: 276 and 280, 178 and 187; at 16^3x32 4 is faster, 48 and 57).  Waves per SIMD do
+//    not decide it: FP64 holds one at every count (268 to 419 registers), FP32 three at 2 per lane and two at 1, 4
+//    and 8, FP16 two at 2 per lane and three at the others.  The FP16 kernel of 12-real links at 8 per lane keeps 120
+//    bytes per lane in scratch memory, with 213 registers and none spilled.
 //  * Fewer while that leaves less than two waves per SIMD (16^3x32 x 4, FP32: 25 us at 2 per lane, 28 at 4).  An FP64
-//    launch holds one wave per SIMD, 1024 at once, and one that fits is not split over more (12^4 x 24: 20 us at 4
-//    per lane, 972 waves, 31 at 1, four rounds of waves; 10x14x18x22 x 8: 22 us at 4, 36 at 1; the normal operator of
+//    launch holds one wave per SIMD, 1024 at once, and one that fits is not split over more (12^4 x 24: 28 us at 4
+//    per lane, 972 waves, 42 at 1, four rounds of waves; 10x14x18x22 x 8: 22 us at 4, 36 at 1; the normal operator of
 //    16^3x32 with 18-real links, x 2: 61 us at 2 per lane, 75 at 1, where a repeated one-parity operator, whose links
 //    stay in the 256 MB cache, takes 30 and 28).
 //  * Counts that are no multiple of 4 or 8 mask lanes of the last group instead of taking one or two per lane, where
 //    that leaves at most two thirds of the groups: links are read, and x, y neighbours found in L1, once per
 //    group.  28^3x96: 3 RHS FP64 739 -> 500 us, FP32 405 -> 313, FP16 247 -> 190; 5 RHS 982 -> 582, 609 -> 394,
-//    378 -> 306; 7 RHS 1283 -> 728; 9 RHS 1582 -> 960.  8 per lane only if the last lane has 5 or more (9 RHS:
+//    378 -> 262; 7 RHS 1283 -> 728; 9 RHS 1582 -> 960.  8 per lane only if the last lane has 5 or more (9 RHS:
 //    1072 us at 8 per lane, 960 at 4; 12: 1168 and 1105).  Enough waves must remain to hide the longer lane:
 //    2048 in FP64 (16^3x32 x 5: 51 -> 43 us), 5120 in FP32 (20^3x40 x 3, 2500 waves: 57 us masked, 50 not), 7168
 //    in FP16 (24^3x48 x 3, 5184 waves: 70 and 64), where 2 per lane gains nothing (64 -> 62..67).

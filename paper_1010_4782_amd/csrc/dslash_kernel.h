@@ -5,9 +5,11 @@
 //   out_p(n) = sum_{k<16} L_k(n) in_{1-p}(n + delta_k),  delta_k in {+-mu, +-3mu}
 //
 // L_k are the packed, phase-, sign- and c_N-folded matrices (pack.hip).  The
-// link stream is the compulsory traffic (16 x 144 B per site in FP64) and is
-// read with non-temporal loads; neighbour colour vectors come through L1/L2,
-// which the XCD-aware block order keeps local.  With 8 right-hand sides the
+// link stream is the compulsory traffic (16 x 144 B per site in FP64), read
+// with non-temporal loads where one workgroup serves all right-hand sides of
+// its sites and with ordinary ones where several read the same links;
+// neighbour colour vectors come through L1/L2, which the XCD-aware block order
+// keeps local.  With 8 right-hand sides the
 // loads of a site's 16 neighbours x R vectors keep the CU's vector-memory
 // address and data units nearly always busy, mostly waiting on lines from
 // beyond L2: the loads each CU keeps in flight, more than HBM, set the pace.  The output (and the epilogue's
@@ -72,8 +74,8 @@ template <int P, int R> constexpr int dslash_pf_r() {
   if (R == 1) return dslash_pf<P>();
   if (P == P16) return R == 2 ? 8 : (R == 4 ? 4 : 2);
   // FP32 and FP64, measured at 48^3x144 x 8 RHS: 4 and 2 links ahead at R = 4 and 8 (FP64: 7.1 and
-  // 5.6 ms per launch against 8.1 and 6.4 ms at 2 and 1, although the deeper pipeline leaves one wave
-  // per SIMD at R = 8; FP32: 3.40 and 2.81 ms against 3.46 and 2.91 ms)
+  // 5.6 ms per launch against 8.1 and 6.4 ms at 2 and 1; FP32: 3.40 and 2.81 ms against 3.46 and 2.91 ms).
+  // Every FP64 kernel here holds one wave per SIMD (268 to 419 registers)
   return R == 2 ? 4 : (R == 4 ? 4 : 2);
 }
 

@@ -72,7 +72,8 @@ __device__ __forceinline__ unsigned short f16_code_y(double v, double s, double 
 // lane per matrix would touch 64 cache lines per load.
 // The FP16 scales need all eight matrices of a group (largest |re|, |im| over the stored entries of an output
 // site's one-hop and, separately, three-hop matrices, rounded to binary32), so with FP16 a lane's four stay in
-// registers (144 VGPRs) instead of being read back from the FP64 blocks.
+// registers (144 of 256 VGPRs; 9 or 10 others of the kernel spill, 40 or 44 bytes per lane) instead of being read
+// back from the FP64 blocks.
 // Lanes past the lattice pack site 0 into the padding, which nothing reads.
 // Bound by its traffic: 8.2 GB beyond L2 at 28^3x96 (FP64 + FP16, two-row long links: 5 GB of it the packed
 // links) in 1.63 ms, 5 TB/s.  One pass per parity and precision, a lane per output site gathering 144-byte
