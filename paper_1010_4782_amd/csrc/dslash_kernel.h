@@ -188,32 +188,28 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
   const Batch& B = A.B;
   // Asked for one by one where a branch first needs them, the launch's parameters are a chain of round trips to
   // memory in front of every wave (28^3x96 x 2, FP16: a launch that finds every right-hand side stopped takes 6.9
-  // us).  FP32 and FP16 ask for them at once: an FP16 iteration of 8^4 takes 32 us instead of 37, of 16^3x32 x 4
-  // 77 instead of 83, of 28^3x96 303 instead of 308.  FP64 is better off with the chain on large lattices
-  // (28^3x96 x 2, 18-real links: 1155 us an iteration, 1190 without).
-  int nblk = gridDim.x, wg = blockDim.x, inl_arg = A.inl, nprob = B.nprob, groups = B.groups[0];
-  if constexpr (P != P64) asm volatile("" : "+s"(nblk), "+s"(wg), "+s"(nzb), "+s"(inl_arg), "+s"(nprob), "+s"(groups));
+  // us).  FP32 and FP16 with one or two per lane ask for them at once: an FP16 iteration of 8^4 takes 32 us instead
+  // of 37, of 16^3x32 x 4 77 instead of 83, of 28^3x96 303 instead of 308.  Longer lanes and FP64 are better off
+  // with the chain on large lattices (FP16, three lattices at 4 per lane: 290 us a launch and 294; FP64, 28^3x96 x 2
+  // with 18-real links: 1155 us an iteration and 1190).
+  constexpr bool kAtOnce = P != P64 && R <= 2;
+  int nblk = gridDim.x, wg = blockDim.x, inl_arg = A.inl, nprob = B.nprob, groups0 = B.groups[0];
+  if constexpr (kAtOnce)
+    asm volatile("" : "+s"(nblk), "+s"(wg), "+s"(nzb), "+s"(inl_arg), "+s"(nprob), "+s"(groups0));
   const bool sweep = nzb < 0;
   const int bid = sweep ? (int)(blockIdx.x >> 3) : xcd_remap(blockIdx.x, nblk);
   const bool inl = inl_arg != 0;
-  int p = 0, start = 0;
-  if (P == P64) {
-    p = inl ? 0 : find_problem(B, bid);
-  } else if (nprob > 1) {
-    p = find_problem(B, bid);
-  }
-  if (P == P64 || nprob > 1) {
-    start = B.block_start[p];
-    groups = B.groups[p];
-  }
+  const bool first = kAtOnce && nprob == 1;
+  const int p = inl || first ? 0 : find_problem(B, bid);
   const cptr<ProbDev> pd = inl ? kernarg_problem() : (cptr<ProbDev>)(B.probs + p);
-  int nrhs = pd->nrhs, slot0 = pd->slot0;
   const Geo g = load_geo(pd);
-  if constexpr (P != P64) asm volatile("" : "+s"(nrhs), "+s"(slot0));
   auto vec = [&](int id) { return reinterpret_cast<char*>(pd->vec[id]); };
-  const int local = bid - start;
+  const int local = first ? bid : bid - B.block_start[p];
+  const int groups = first ? groups0 : B.groups[p];
   const int pos = local / groups;
   const int r0 = (local - pos * groups) * R;
+  int nrhs = pd->nrhs, slot0 = pd->slot0;
+  if constexpr (kAtOnce) asm volatile("" : "+s"(nrhs), "+s"(slot0));
   const int tile = sweep ? xcd_sweep_tile(pos, g, wg) : (nzb ? xcd_block_tile(pos, g, wg, nzb) : pos);
   if (tile < 0) return;  // uniform: an unused position of the sweep
 
