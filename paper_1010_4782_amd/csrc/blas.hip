@@ -578,7 +578,7 @@ hipError_t launch_finalize(const BatchHost& bh, int what, int kind, int gate, in
 // The sites of one time slice and parity are the contiguous even-odd range [t * slice, (t + 1) * slice).
 // One workgroup per (group, slice) sums its slice in a fixed order: the result does not depend on the
 // launch.  FP64.  A slice is read as plain 16-byte words, 16 waves with four words each in flight: there are
-// only as many workgroups as slices and groups (28^3x96, 4 groups of 3: 606 MB in 116 us; four waves reading
+// only as many workgroups as slices and groups (28^3x96, 4 groups of 3: 606 MB in 112 us; four waves reading
 // one 48-byte vector at a time took 164).
 constexpr int kSliceWG = 1024;
 __global__ __launch_bounds__(kSliceWG) void k_slice_norm2(const char* v, const double* n2, long half, int slice,

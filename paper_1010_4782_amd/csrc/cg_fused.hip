@@ -8,7 +8,7 @@
 //   k_resid  alpha from the <d, Ad> partials; r -= alpha Ad; |r|^2 partials
 //   k_xd     beta from the |r|^2 partials and the stopping test; x += alpha d; d = r + beta d
 // Every sum and product is taken in the order and precision of the general kernels: the same bits.  An FP64
-// iteration at 8^4 takes 24.4 us instead of 32.9, an FP16 one at 16^3x32 46.0 instead of 52.8.  Forming
+// iteration at 8^4 takes 25 us instead of 37, an FP16 one at 16^3x32 44 instead of 54.  Forming
 // r + beta d inside the first operator launch too (three launches) was slower from 12^4 on: 33.8 us against
 // 29.4, the reads of two vectors at 16 neighbours cost more than a launch.
 //
@@ -206,9 +206,9 @@ __global__ __launch_bounds__(kMaxWG) void k_xd(Batch B, Scal* next, int x_id, in
 // of its slot, lane t the partials t, t + 1024, ... as k_finalize does, then walks its share of the slot's
 // vectors.  Such a launch reads the partials once per workgroup (24^3x48: 41 KB, 10 MB in all, from L2) while its
 // first sites are on their way, where the general path waits for a one-workgroup launch (6.4 us) twice an
-// iteration.  An iteration takes, general -> wide: 24^3x48 FP16 112.8 -> 106.2 us, FP64 272 -> 266; 20^3x40 x 4
-// FP16 123.1 -> 115.9; 32^3x64 FP32 497 -> 490; 28^3x96 FP16 270.1 -> 267.9.  With 512 workgroups the sums cost
-// more than the second workgroup per CU gives: 109.9 us (24^3x48 FP16), 274.5 (28^3x96).
+// iteration.  An iteration takes, general -> wide: 24^3x48 FP16 111 -> 103 us, FP64 270 -> 262; 20^3x40 x 4
+// FP16 122 -> 114; 32^3x64 FP32 451 -> 443; 28^3x96 FP16 270 -> 266.  With 512 workgroups the sums cost more than
+// the second workgroup per CU gives: 3.5% on 24^3x48 in FP16, 2.5% on 28^3x96.
 constexpr int kWideUnroll = 24;   // partials a lane has in flight
 
 __device__ __forceinline__ double wide_sum(const double* src, int n, double* lds /* >= 16 */) {
