@@ -117,11 +117,11 @@ hipError_t iteration(Run& R, int x_prec, int x_id, double* d_hist) {
 //    64 MiB of partials an iteration on (24: 191 and 193, 32: 257 and 254, 64: 464 and 444).
 //  * The wide kernels hold one workgroup per CU and are no faster where a launch is bound by memory rather than by
 //    latency (2^21 sites: 32^3x64 with two right-hand sides, FP16, 401 and 403; 24^3x48 with 6, 304 and 305).
-//    With many right-hand sides the tiles divide less evenly over the CUs, which FP64 still gains from (16^3x40
-//    with 22: 460 and 463) and FP32 and FP16 do not (FP32, 17: 250 and 246, 22: 324 and 314; FP16, 22: 259 and
-//    256; 20^3x40 with 13: 355 and 357, 266 and 271).
+//    With many right-hand sides and more than 2^20 sites FP64 still gains (16^3x40 with 22: 460 and 463), FP32 and
+//    FP16 do not (FP32, 17: 250 and 246, 22: 324 and 314; FP16, 22: 259 and 256; 20^3x40 with 13: 355 and 357, 266
+//    and 271); with fewer sites they do (18 over three lattices, 0.7 million: FP32 1.3%).
 // Sampled profiles keep the general path.
-constexpr long kWideSites = 1L << 21;
+constexpr long kWideSites = 1L << 21, kWideSitesManyLow = 1L << 20;
 constexpr int kWideSlotsLow = 16;
 constexpr double kPartialBytesF16 = 64.0 * 1024 * 1024;
 enum Path { kGeneral, kSmall, kWide };
@@ -139,9 +139,9 @@ Path iteration_path(const Run& R) {
     tiles.push_back(ceil_div(p.half, kWideWG));
     slots.push_back(p.nrhs);
   }
-  const bool low = R.prec != P64;
+  const bool many_low = R.prec != P64 && R.bh.nslots > kWideSlotsLow;
   if (most <= kFusedTiles) return R.prec == P16 && partials >= kPartialBytesF16 ? kGeneral : kSmall;
-  if (sites > kWideSites || (low && R.bh.nslots > kWideSlotsLow)) return kGeneral;
+  if (sites > (many_low ? kWideSitesManyLow : kWideSites)) return kGeneral;
   return wide_tiles(tiles.data(), slots.data(), (int)tiles.size()) ? kWide : kGeneral;
 }
 
