@@ -193,12 +193,19 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
   // with the chain on large lattices (FP16, three lattices at 4 per lane: 290 us a launch and 294; FP64, 28^3x96 x 2
   // with 18-real links: 1155 us an iteration and 1190).
   constexpr bool kAtOnce = P != P64 && R <= 2;
-  int nblk = gridDim.x, wg = blockDim.x, inl_arg = A.inl, nprob = B.nprob, groups0 = B.groups[0];
-  if constexpr (kAtOnce)
-    asm volatile("" : "+s"(nblk), "+s"(wg), "+s"(nzb), "+s"(inl_arg), "+s"(nprob), "+s"(groups0));
+  int nblk = 0, wg0 = 0, inl0 = 0, nprob = 0, groups0 = 0;
+  if constexpr (kAtOnce) {
+    nblk = gridDim.x;
+    wg0 = blockDim.x;
+    inl0 = A.inl;
+    nprob = B.nprob;
+    groups0 = B.groups[0];
+    asm volatile("" : "+s"(nblk), "+s"(wg0), "+s"(nzb), "+s"(inl0), "+s"(nprob), "+s"(groups0));
+  }
+  auto wg = [&] { return kAtOnce ? (unsigned)wg0 : blockDim.x; };
   const bool sweep = nzb < 0;
-  const int bid = sweep ? (int)(blockIdx.x >> 3) : xcd_remap(blockIdx.x, nblk);
-  const bool inl = inl_arg != 0;
+  const int bid = sweep ? (int)(blockIdx.x >> 3) : xcd_remap(blockIdx.x, kAtOnce ? nblk : (int)gridDim.x);
+  const bool inl = (kAtOnce ? inl0 : A.inl) != 0;
   const bool first = kAtOnce && nprob == 1;
   const int p = inl || first ? 0 : find_problem(B, bid);
   const cptr<ProbDev> pd = inl ? kernarg_problem() : (cptr<ProbDev>)(B.probs + p);
@@ -210,7 +217,7 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
   const int r0 = (local - pos * groups) * R;
   int nrhs = pd->nrhs, slot0 = pd->slot0;
   if constexpr (kAtOnce) asm volatile("" : "+s"(nrhs), "+s"(slot0));
-  const int tile = sweep ? xcd_sweep_tile(pos, g, wg) : (nzb ? xcd_block_tile(pos, g, wg, nzb) : pos);
+  const int tile = sweep ? xcd_sweep_tile(pos, g, wg()) : (nzb ? xcd_block_tile(pos, g, wg(), nzb) : pos);
   if (tile < 0) return;  // uniform: an unused position of the sweep
 
   bool on[R];
@@ -222,7 +229,7 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
   }
   if (!any) return;  // uniform over the workgroup
 
-  const int cb_raw = tile * wg + threadIdx.x;
+  const int cb_raw = tile * wg() + threadIdx.x;
   const bool live = cb_raw < g.half;
   const int cb = live ? cb_raw : g.half - 1;  // dead lanes read a valid site and store nothing
   const Site s = site_of(cb, out_par, g);
@@ -250,8 +257,8 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
     for (int c = 0; c < 3; ++c) acc[r][c] = Cx<T>{T(0), T(0)};
 
   // LDS window: sites [w0, w0 + wn) of every active RHS, 8-byte units, loaded by the whole workgroup
-  const int w0 = tile * wg - window_margin(g.Xh);
-  const int wn = wg + 2 * window_margin(g.Xh);
+  const int w0 = tile * (int)wg() - window_margin(g.Xh);
+  const int wn = (int)wg() + 2 * window_margin(g.Xh);
   constexpr int SB = spinor_bytes(P);
   if constexpr (LDS) {
     const int units = wn * SB / 8;
@@ -261,7 +268,7 @@ __global__ __launch_bounds__(kMaxWG) void k_dslash(DslashArgs A, int out_par, in
       // window sites outside [0, in_half) are never read back: every neighbour index is in range
       const char* src = in + r * rstride_in;
       char* dst = dslash_window + r * wn * SB;
-      for (int u = threadIdx.x; u < units; u += wg) {
+      for (int u = threadIdx.x; u < units; u += wg()) {
         const int site = w0 + (u * 8) / SB;
         if (site >= 0 && site < g.in_half)
           *reinterpret_cast<u2v*>(dst + u * 8) = *as_global<u2v>(src + (long)w0 * SB + (long)u * 8);
