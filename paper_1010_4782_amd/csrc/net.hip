@@ -139,8 +139,8 @@ __device__ __forceinline__ void transported(const NetView& a, const Site& s, lon
   }
 }
 
-// Layers with one channel on a side.  Large lattices are bound by the reads of the links (24^3x48: 382 MB of
-// 510, 8 -> 1 in 80 us, 1 -> 8 in 58), small ones by the chain of load latencies: the next direction's link and
+// Layers with one channel on a side.  Large lattices are bound by reads (24^3x48: 1 -> 8 335 MB, 191 of it links,
+// in 58 us; 8 -> 1 327 MB in 80 us, its neighbours read eight times through L2), small ones by the chain of load latencies: the next direction's link and
 // channels are in flight while a direction is transported and mixed, in single-wave workgroups, so that a small
 // lattice spreads over more CUs.  Without that 8 -> 1 took 96 us, and a whole network call with 1, 8, 8 and 1
 // channels at 8^4 45 us instead of 39, with 1, 4 and 1 at 10x8x8x14 28 instead of 19.  XCD ranges of whole link
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kNetVecWG) void k_net_layer(NetLaunch l) {
 // bound the kernel; the rest has to stay out of their way.  One stage is one channel pair of one term: its
 // four components go to the operand layout through LDS (12 four-byte writes, 3 sixteen-byte reads, free of
 // bank conflicts) while the products of the stage before run, and the pair's registers take the loads of
-// the next term at once.  Both parities of an 8-channel layer at 24^3x48 take 182 to 194 us (145 us with every
+// the next term at once.  Both parities of an 8-channel layer at 24^3x48 take 180 to 194 us (145 us with every
 // load left out, 82 us without the products too); two launches in launch order of the sites, whose operand reads
 // waited out an LDS latency for each pair of products, took 272 us.
 template <int CIN, int COUT>
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(256) void k_net_wgrad(NetLaunch l, double* partial,
 // [channel][k of the step][step], so that a lane reads the operands of four consecutive steps with one
 // 16-byte load.  Row strides of 196 floats spread the 16 rows over the banks; the rows were 384 floats apart
 // before, all on one bank, and those conflicts were 60% of the launch.  The loads of the next 32 sites are in
-// flight during the products.  Both parities of an 8-channel layer at 24^3x48 take 290 us; with one direction
+// flight during the products.  Both parities of an 8-channel layer at 24^3x48 take 283 to 293 us; with one direction
 // per workgroup, half the columns empty, 655 us.
 constexpr int kWgradMfmaWG = 128;
 
